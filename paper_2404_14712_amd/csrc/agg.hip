@@ -13,6 +13,7 @@
 #include <algorithm>
 
 #include "agg.h"
+#include "agg_stream.h"
 #include "gemm.h"
 #include "kernels.h"
 #include "tile.h"
@@ -127,11 +128,17 @@ __global__ void __launch_bounds__(256) agg_gemv_final(const float* __restrict__ 
 // and lane h adds the dh / 8 chunks of head h in order. A row is taken in
 // passes of whole heads, at most kFoldMaxChunks chunks each.
 constexpr int kFoldMaxChunks = 1024;
+// Block 0 also keeps a copy of b_v (16-byte pieces): the streaming backward
+// takes it off the stored value outputs.
 template <typename T>
 __global__ void __launch_bounds__(256) agg_fold_key(const T* __restrict__ wk, const float* __restrict__ q,
-                                                    T* __restrict__ Ut, int d, int H, int dh) {
+                                                    T* __restrict__ Ut, const T* __restrict__ bv, T* __restrict__ bv_out,
+                                                    int d, int H, int dh) {
   __shared__ float part[4][kFoldMaxChunks];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  if (blockIdx.x == 0 && bv_out)
+    for (int j = threadIdx.x; j < H * dh * (int)sizeof(T) / 16; j += 256)
+      st128(reinterpret_cast<char*>(bv_out) + j * 16, ld128(reinterpret_cast<const char*>(bv) + j * 16));
   const int i = blockIdx.x * 4 + wave;
   const int per = dh / 8, hp = kFoldMaxChunks / per;  // chunks per head, heads per pass
   const T* row = wk + (int64_t)i * H * dh;
@@ -629,9 +636,10 @@ Sizes sizes(const orbit_agg_desc& a) {
 }
 size_t esz(orbit_dtype dt) { return dt == ORBIT_BF16 ? 2 : 4; }
 
-// saved layout: q f32 [A] | Ut [H, d] | a32 [T, H, V] | xbar [T, H, d] | zh [T, A]
+// saved layout: q f32 [A] | Ut [H, d] | a32 [T, H, V] ([T, V, H] on the streaming path) | xbar [T, H, d]
+//               | zh [T, A] | b_v [A] (streaming path)
 struct Saved {
-  float* q; void* Ut; float* a32; void* xbar; void* zh;
+  float* q; void* Ut; float* a32; void* xbar; void* zh; void* bv;
 };
 Saved carve_saved(const Sizes& z, orbit_dtype dt, void* base, size_t* used) {
   Carver c(base);
@@ -641,6 +649,7 @@ Saved carve_saved(const Sizes& z, orbit_dtype dt, void* base, size_t* used) {
   s.a32 = c.take<float>((size_t)z.T * z.H * z.V);
   s.xbar = c.take<char>((size_t)z.T * z.H * z.d * esz(dt));
   s.zh = c.take<char>((size_t)z.T * z.A * esz(dt));
+  s.bv = agg_stream_ok(dt, z.V, z.d, z.H) ? c.take<char>((size_t)z.A * esz(dt)) : nullptr;
   if (used) *used = c.used();
   return s;
 }
@@ -689,8 +698,9 @@ size_t agg_saved_bytes(const orbit_agg_desc& a) {
 }
 
 // forward workspace: S f32 [T*V, H] | ab [T, H, Vp] | query partials | gemm split-K
-// backward workspace: dzh [T, A] | dxbar [T, H, d] | da f32 [T, H, V] | ac [T*V, 2H] | dU f32 [d, H]
-//                     | dq f32 [A] | query-gradient partials | colsum | gemm split-K
+// backward workspace: dzh [T, A] | dxbar [T, H, d] | da f32 [T, H, V] | ac [T*V, 2H] (streaming path: row sums f32
+//                     [T, 16] | dU partials) | dU f32 [d, H] | dq f32 [A] | query-gradient partials | colsum
+//                     | gemm split-K
 static size_t gemm_ws_max(const Sizes& z, orbit_dtype dt) {
   // split-K partials of every product of the forward and backward passes
   const int T = (int)z.T, TV = (int)(z.T * z.V);
@@ -717,11 +727,17 @@ size_t agg_workspace_bytes(const orbit_agg_desc& a) {
   f.take<char>((size_t)z.T * z.H * z.Vp * esz(dt));
   f.take<char>(gemv_part_bytes(z.d, z.A));
   size_t fwd = f.used();
+  const bool stream = agg_stream_ok(dt, z.V, z.d, z.H);
   Carver b(nullptr);
   b.take<char>((size_t)z.T * z.A * esz(dt));
   b.take<char>((size_t)z.T * z.H * z.d * esz(dt));
-  b.take<float>((size_t)z.T * z.H * z.V);
-  b.take<char>((size_t)z.T * z.V * 2 * z.H * esz(dt));
+  if (stream) {
+    b.take<float>((size_t)z.T * 16);
+    b.take<float>((size_t)agg_stream_blocks(z.T, z.d) * z.H * agg_stream_cols(z.d));
+  } else {
+    b.take<float>((size_t)z.T * z.H * z.V);
+    b.take<char>((size_t)z.T * z.V * 2 * z.H * esz(dt));
+  }
   b.take<float>((size_t)z.d * z.H);
   b.take<float>((size_t)z.A);
   b.take<char>(gemv_part_bytes(z.d, z.A));
@@ -749,54 +765,61 @@ orbit_status agg_forward(const orbit_agg_desc& a, const void* tok, const orbit_a
   if (dt == ORBIT_BF16) {
     ORBIT_TRY((gemv_cols<bf16, false>("agg_query", p.w_q, p.q0, nullptr, p.b_q, sv.q, gvp, z.d, z.A, z.H, z.dh, s)));
     ORBIT_TRY(launch(ku, agg_fold_key<bf16>, dim3((unsigned)cdiv(z.d, 4)), dim3(256), 0, s, (const bf16*)p.w_k,
-                     (const float*)sv.q, (bf16*)sv.Ut, z.d, z.H, z.dh));
+                     (const float*)sv.q, (bf16*)sv.Ut, (const bf16*)p.b_v, (bf16*)sv.bv, z.d, z.H, z.dh));
   } else {
     ORBIT_TRY((gemv_cols<float, false>("agg_query", p.w_q, p.q0, nullptr, p.b_q, sv.q, gvp, z.d, z.A, z.H, z.dh, s)));
     ORBIT_TRY(launch(ku, agg_fold_key<float>, dim3((unsigned)cdiv(z.d, 4)), dim3(256), 0, s,
-                     (const float*)p.w_k, (const float*)sv.q, (float*)sv.Ut, z.d, z.H, z.dh));
+                     (const float*)p.w_k, (const float*)sv.q, (float*)sv.Ut, (const float*)nullptr,
+                     (float*)nullptr, z.d, z.H, z.dh));
   }
-  // 2. scores S[t*V+v][h] = x_{t,v} . u_h / sqrt(dh)
-  if (rowdot_ok(dt, z, tok, sv.Ut)) {
-    ORBIT_TRY(rowdot("agg_scores", z, tok, sv.Ut, 0, S, (int64_t)z.V * z.H, z.H, 1, 1.f / sqrtf((float)z.dh), s));
+  if (agg_stream_ok(dt, z.V, z.d, z.H)) {
+    // 2.-4. in one pass over the tokens
+    ORBIT_TRY(agg_stream_fwd(static_cast<const bf16*>(tok), static_cast<const bf16*>(sv.Ut), sv.a32,
+                             static_cast<bf16*>(sv.xbar), z.T, z.V, z.d, z.H, 1.f / sqrtf((float)z.dh), s));
   } else {
-    Gemm g = base_gemm(dt);
-    g.tag = "agg_scores";
-    g.A = tok; g.lda = z.d; g.a_kmajor = true;
-    g.B = sv.Ut; g.ldb = z.d; g.b_kmajor = true;
-    g.C = S; g.ldc = z.H; g.out_f32 = true;
-    g.M = (int)TV; g.N = z.H; g.K = z.d;
-    g.alpha = 1.f / sqrtf((float)z.dh);
-    g.stream = true;  // the token tensor is read once here
-    ORBIT_TRY(gemm(g, gws, gws_bytes, s));
-  }
-  // 3. softmax over variables
-  KernelInfo ks{"agg_softmax", 0.0, (double)TV * z.H * 8};
-  if (dt == ORBIT_BF16)
-    ORBIT_TRY(launch(ks, agg_softmax<bf16>, dim3((unsigned)cdiv(z.T, 4)), dim3(256), 0, s, (const float*)S, sv.a32,
-                     (bf16*)ab, z.T, z.V, z.Vp, z.H));
-  else
-    ORBIT_TRY(launch(ks, agg_softmax<float>, dim3((unsigned)cdiv(z.T, 4)), dim3(256), 0, s, (const float*)S, sv.a32,
-                     (float*)ab, z.T, z.V, z.Vp, z.H));
-  // 4. xbar_t = a_t [H, V] X_t [V, d]   (batched over tokens)
-  if (dt == ORBIT_BF16 && (z.H == 8 || z.H == 16)) {
-    const int64_t items = z.T * cdiv(z.d, 512);
-    KernelInfo kx{"agg_xbar", 2.0 * z.T * z.H * (double)z.V * z.d,
-                  (double)z.T * (z.V + z.H) * z.d * 2.0};
-    const dim3 grid((unsigned)cdiv(items, 4));
-    if (z.H == 8)
-      ORBIT_TRY(launch(kx, agg_xbar<8>, grid, dim3(256), 0, s, (const bf16*)ab, (const bf16*)tok, (bf16*)sv.xbar,
-                       z.T, z.V, z.Vp, z.d));
+    // 2. scores S[t*V+v][h] = x_{t,v} . u_h / sqrt(dh)
+    if (rowdot_ok(dt, z, tok, sv.Ut)) {
+      ORBIT_TRY(rowdot("agg_scores", z, tok, sv.Ut, 0, S, (int64_t)z.V * z.H, z.H, 1, 1.f / sqrtf((float)z.dh), s));
+    } else {
+      Gemm g = base_gemm(dt);
+      g.tag = "agg_scores";
+      g.A = tok; g.lda = z.d; g.a_kmajor = true;
+      g.B = sv.Ut; g.ldb = z.d; g.b_kmajor = true;
+      g.C = S; g.ldc = z.H; g.out_f32 = true;
+      g.M = (int)TV; g.N = z.H; g.K = z.d;
+      g.alpha = 1.f / sqrtf((float)z.dh);
+      g.stream = true;  // the token tensor is read once here
+      ORBIT_TRY(gemm(g, gws, gws_bytes, s));
+    }
+    // 3. softmax over variables
+    KernelInfo ks{"agg_softmax", 0.0, (double)TV * z.H * 8};
+    if (dt == ORBIT_BF16)
+      ORBIT_TRY(launch(ks, agg_softmax<bf16>, dim3((unsigned)cdiv(z.T, 4)), dim3(256), 0, s, (const float*)S, sv.a32,
+                       (bf16*)ab, z.T, z.V, z.Vp, z.H));
     else
-      ORBIT_TRY(launch(kx, agg_xbar<16>, grid, dim3(256), 0, s, (const bf16*)ab, (const bf16*)tok, (bf16*)sv.xbar,
-                       z.T, z.V, z.Vp, z.d));
-  } else {
-    Gemm g = base_gemm(dt);
-    g.tag = "agg_xbar";
-    g.A = ab; g.lda = z.Vp; g.a_kmajor = true; g.sA = (int64_t)z.H * z.Vp;
-    g.B = tok; g.ldb = z.d; g.b_kmajor = false; g.sB = (int64_t)z.V * z.d;
-    g.C = sv.xbar; g.ldc = z.d; g.sC = (int64_t)z.H * z.d;
-    g.M = z.H; g.N = z.d; g.K = z.V; g.batch = (int)z.T;
-    ORBIT_TRY(gemm(g, gws, gws_bytes, s));
+      ORBIT_TRY(launch(ks, agg_softmax<float>, dim3((unsigned)cdiv(z.T, 4)), dim3(256), 0, s, (const float*)S, sv.a32,
+                       (float*)ab, z.T, z.V, z.Vp, z.H));
+    // 4. xbar_t = a_t [H, V] X_t [V, d]   (batched over tokens)
+    if (dt == ORBIT_BF16 && (z.H == 8 || z.H == 16)) {
+      const int64_t items = z.T * cdiv(z.d, 512);
+      KernelInfo kx{"agg_xbar", 2.0 * z.T * z.H * (double)z.V * z.d,
+                    (double)z.T * (z.V + z.H) * z.d * 2.0};
+      const dim3 grid((unsigned)cdiv(items, 4));
+      if (z.H == 8)
+        ORBIT_TRY(launch(kx, agg_xbar<8>, grid, dim3(256), 0, s, (const bf16*)ab, (const bf16*)tok, (bf16*)sv.xbar,
+                         z.T, z.V, z.Vp, z.d));
+      else
+        ORBIT_TRY(launch(kx, agg_xbar<16>, grid, dim3(256), 0, s, (const bf16*)ab, (const bf16*)tok, (bf16*)sv.xbar,
+                         z.T, z.V, z.Vp, z.d));
+    } else {
+      Gemm g = base_gemm(dt);
+      g.tag = "agg_xbar";
+      g.A = ab; g.lda = z.Vp; g.a_kmajor = true; g.sA = (int64_t)z.H * z.Vp;
+      g.B = tok; g.ldb = z.d; g.b_kmajor = false; g.sB = (int64_t)z.V * z.d;
+      g.C = sv.xbar; g.ldc = z.d; g.sC = (int64_t)z.H * z.d;
+      g.M = z.H; g.N = z.d; g.K = z.V; g.batch = (int)z.T;
+      ORBIT_TRY(gemm(g, gws, gws_bytes, s));
+    }
   }
   // 5. zh_h = xbar_h W_v^h + b_v^h   (batched over heads)
   {
@@ -833,8 +856,16 @@ orbit_status agg_backward(const orbit_agg_desc& a, const void* tok, const orbit_
   Carver w(ws);
   void* dzh = w.take<char>((size_t)z.T * z.A * esz(dt));
   void* dxbar = w.take<char>((size_t)z.T * z.H * z.d * esz(dt));
-  float* da = w.take<float>((size_t)z.T * z.H * z.V);
-  void* ac = w.take<char>((size_t)z.T * z.V * 2 * z.H * esz(dt));
+  const bool stream = agg_stream_ok(dt, z.V, z.d, z.H);
+  float *da = nullptr, *rowsum = nullptr, *du_part = nullptr;
+  void* ac = nullptr;
+  if (stream) {
+    rowsum = w.take<float>((size_t)z.T * 16);
+    du_part = w.take<float>((size_t)agg_stream_blocks(z.T, z.d) * z.H * agg_stream_cols(z.d));
+  } else {
+    da = w.take<float>((size_t)z.T * z.H * z.V);
+    ac = w.take<char>((size_t)z.T * z.V * 2 * z.H * esz(dt));
+  }
   float* dU = w.take<float>((size_t)z.d * z.H);
   float* dq = w.take<float>((size_t)z.A);
   float* gvp = w.take<float>(gemv_part_bytes(z.d, z.A) / sizeof(float));
@@ -914,35 +945,44 @@ orbit_status agg_backward(const orbit_agg_desc& a, const void* tok, const orbit_
     g.M = (int)z.T; g.N = z.d; g.K = z.dh; g.batch = z.H;
     ORBIT_TRY(gemm(g, gws, gws_bytes, s));
   }
-  // da_t [H, V] = dxbar_t [H, d] X_t^T
-  if (rowdot_ok(dt, z, tok, dxbar)) {
-    ORBIT_TRY(rowdot("agg_da", z, tok, dxbar, (int64_t)z.H * z.d, da, (int64_t)z.H * z.V, 1, z.V, 1.f, s));
+  if (stream) {
+    const bf16* zh = static_cast<const bf16*>(sv.zh);
+    ORBIT_TRY(agg_stream_rowsum(zh, static_cast<const bf16*>(dzh), static_cast<const bf16*>(sv.bv), rowsum, z.T, z.H,
+                                z.dh, s));
+    ORBIT_TRY(agg_stream_bwd(static_cast<const bf16*>(tok), static_cast<const bf16*>(dxbar),
+                             static_cast<const bf16*>(sv.Ut), sv.a32, rowsum, static_cast<const bf16*>(sv.xbar),
+                             static_cast<bf16*>(dtok), du_part, dU, z.T, z.V, z.d, z.H, scale, s));
   } else {
-    Gemm g = base_gemm(dt);
-    g.tag = "agg_da";
-    g.A = dxbar; g.lda = z.d; g.a_kmajor = true; g.sA = (int64_t)z.H * z.d;
-    g.B = tok; g.ldb = z.d; g.b_kmajor = true; g.sB = (int64_t)z.V * z.d;
-    g.C = da; g.ldc = z.V; g.sC = (int64_t)z.H * z.V; g.out_f32 = true;
-    g.M = z.H; g.N = z.V; g.K = z.d; g.batch = (int)z.T;
-    ORBIT_TRY(gemm(g, gws, gws_bytes, s));
-  }
-  // softmax backward -> ac = [a | ds] per (t, v) row
-  KernelInfo ksb{"agg_softmax_bwd", 0.0, (double)TV * z.H * (8 + 4 * esz(dt))};
-  if (dt == ORBIT_BF16)
-    ORBIT_TRY(launch(ksb, agg_softmax_bwd<bf16>, dim3((unsigned)cdiv(z.T, 4)), dim3(256), 0, s, (const float*)sv.a32,
-                     (const float*)da, (bf16*)ac, z.T, z.V, z.H, scale));
-  else
-    ORBIT_TRY(launch(ksb, agg_softmax_bwd<float>, dim3((unsigned)cdiv(z.T, 4)), dim3(256), 0, s, (const float*)sv.a32,
-                     (const float*)da, (float*)ac, z.T, z.V, z.H, scale));
-  // dU [d, H] = X^T ds  (reduction over all T*V token rows)
-  {
-    Gemm g = base_gemm(dt);
-    g.tag = "agg_du";
-    g.A = tok; g.lda = z.d; g.a_kmajor = false;
-    g.B = static_cast<const char*>(ac) + z.H * esz(dt); g.ldb = 2 * z.H; g.b_kmajor = false;
-    g.C = dU; g.ldc = z.H; g.out_f32 = true;
-    g.M = z.d; g.N = z.H; g.K = (int)TV;
-    ORBIT_TRY(gemm(g, gws, gws_bytes, s));
+    // da_t [H, V] = dxbar_t [H, d] X_t^T
+    if (rowdot_ok(dt, z, tok, dxbar)) {
+      ORBIT_TRY(rowdot("agg_da", z, tok, dxbar, (int64_t)z.H * z.d, da, (int64_t)z.H * z.V, 1, z.V, 1.f, s));
+    } else {
+      Gemm g = base_gemm(dt);
+      g.tag = "agg_da";
+      g.A = dxbar; g.lda = z.d; g.a_kmajor = true; g.sA = (int64_t)z.H * z.d;
+      g.B = tok; g.ldb = z.d; g.b_kmajor = true; g.sB = (int64_t)z.V * z.d;
+      g.C = da; g.ldc = z.V; g.sC = (int64_t)z.H * z.V; g.out_f32 = true;
+      g.M = z.H; g.N = z.V; g.K = z.d; g.batch = (int)z.T;
+      ORBIT_TRY(gemm(g, gws, gws_bytes, s));
+    }
+    // softmax backward -> ac = [a | ds] per (t, v) row
+    KernelInfo ksb{"agg_softmax_bwd", 0.0, (double)TV * z.H * (8 + 4 * esz(dt))};
+    if (dt == ORBIT_BF16)
+      ORBIT_TRY(launch(ksb, agg_softmax_bwd<bf16>, dim3((unsigned)cdiv(z.T, 4)), dim3(256), 0, s, (const float*)sv.a32,
+                       (const float*)da, (bf16*)ac, z.T, z.V, z.H, scale));
+    else
+      ORBIT_TRY(launch(ksb, agg_softmax_bwd<float>, dim3((unsigned)cdiv(z.T, 4)), dim3(256), 0, s, (const float*)sv.a32,
+                       (const float*)da, (float*)ac, z.T, z.V, z.H, scale));
+    // dU [d, H] = X^T ds  (reduction over all T*V token rows)
+    {
+      Gemm g = base_gemm(dt);
+      g.tag = "agg_du";
+      g.A = tok; g.lda = z.d; g.a_kmajor = false;
+      g.B = static_cast<const char*>(ac) + z.H * esz(dt); g.ldb = 2 * z.H; g.b_kmajor = false;
+      g.C = dU; g.ldc = z.H; g.out_f32 = true;
+      g.M = z.d; g.N = z.H; g.K = (int)TV;
+      ORBIT_TRY(gemm(g, gws, gws_bytes, s));
+    }
   }
   // query path
   KernelInfo kou{"agg_outer", 2.0 * z.d * z.A, 8.0 * z.d * z.A};
@@ -962,6 +1002,7 @@ orbit_status agg_backward(const orbit_agg_desc& a, const void* tok, const orbit_
     ORBIT_TRY(launch(kqb, agg_query_bwd<float>, dim3((unsigned)cdiv(z.d, 4)), dim3(256), 0, s,
                      (const float*)p.w_q, (const float*)dq, gr.q0, gr.b_q, gr.b_k, z.d, z.A, accumulate));
   }
+  if (stream) return ORBIT_OK;  // dtok came with dU
   // dtok_t [V, d] = [a^T | ds] [V, 2H] . [dxbar_t ; U^T] [2H, d]   (batched over tokens)
   if (dt == ORBIT_BF16 && z.V <= 96 && (z.H == 8 || z.H == 16 || z.H == 32)) {
     KernelInfo kd{"agg_dtok", 2.0 * z.T * z.V * (double)z.d * 2 * z.H,

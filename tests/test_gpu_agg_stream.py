@@ -1,0 +1,61 @@
+"""The single-pass aggregation kernels (bf16, 8 or 16 heads, embeddings up to
+2048) against the fp64 oracle at the sizes where they can go wrong: embeddings
+around each instantiation's width and not filling it, variables around the
+16-row slots and at the ends of the range, fewer patches than blocks and
+several patches per block; and just outside the range, where the general path
+runs."""
+import numpy as np
+import pytest
+
+import oracle as O
+import synth
+from helpers import TOL, check, dev, host
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # B, L, V, d, heads, head_dim
+    (1, 5, 16, 512, 16, 32),       # exactly one slot per patch
+    (2, 300, 17, 256, 8, 32),      # patches > blocks, a one-row last slot, half-empty columns
+    (1, 530, 3, 520, 8, 24),       # just past 512 columns; fewer variables than a slot
+    (1, 40, 48, 1024, 16, 64),
+    (1, 33, 49, 1032, 16, 16),     # just past 1024 columns
+    (1, 20, 31, 1544, 8, 64),      # just past 1536 columns
+    (1, 12, 128, 2048, 16, 32),    # the largest V and d
+    (1, 270, 2, 2040, 16, 8),
+    (3, 7, 97, 8, 8, 8),           # the smallest d
+    (1, 9, 129, 512, 8, 32),       # V past the range: general path
+    (1, 9, 20, 2056, 16, 32),      # d past the range: general path
+]
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_agg_stream(lib, case):
+    import torch
+    from paper_2404_14712_amd._lib import AggDesc
+    B, L, V, d, H, dh = case
+    c = synth.small_config("115m", dtype="bf16", B=B, L=L, V=V, d=d, agg_heads=H, agg_head_dim=dh, sigma=0.1)
+    tok = synth.normal(c.seed, "tok", (B, L, V, d), dtype="bf16")
+    prm = synth.make_params(c.seed, "agg", synth.agg_param_shapes(d, H * dh, L), 0.1, "bf16")
+    dz = synth.normal(c.seed, "dz", (B, L, d), dtype="bf16")
+    desc = AggDesc(B, L, V, d, H, dh, 1)
+    pd = {k: dev(v, "bf16") for k, v in prm.items()}
+    tokd, dzd = dev(tok, "bf16"), dev(dz, "bf16")
+    z = torch.zeros(B, L, d, dtype=torch.bfloat16, device="cuda")
+    # scratch with NaN bit patterns: nothing unwritten may be read
+    saved = torch.full((lib.orbit_var_aggregate_saved_bytes(desc),), 255, dtype=torch.uint8, device="cuda")
+    ws = torch.full((lib.orbit_var_aggregate_workspace_bytes(desc),), 255, dtype=torch.uint8, device="cuda")
+    # a guard row behind the gradient: no store may pass the last patch
+    dtok = torch.full((B * L * V + 1, d), 7.0, dtype=torch.bfloat16, device="cuda")
+    g = {k: torch.full(v.shape, 7.0, dtype=torch.float32, device="cuda") for k, v in prm.items()}
+    lib.orbit_var_aggregate(desc, tokd, pd, z, saved, ws)
+    lib.orbit_var_aggregate_bwd(desc, tokd, pd, saved, dzd, dtok, g, 0, ws)
+    torch.cuda.synchronize()
+    ref, cache = O.agg_fwd(tok, prm, H)
+    rdtok, rg = O.agg_bwd(dz, cache, prm)
+    tol = TOL["bf16"]
+    check("z", host(z), ref, tol)
+    check("dtok", host(dtok[:-1]).reshape(rdtok.shape), rdtok, tol)
+    assert bool((dtok[-1] == 7.0).all())
+    for k in rg:
+        check(f"d{k}", host(g[k]), rg[k], tol, floor_ref=rg["b_q"])
