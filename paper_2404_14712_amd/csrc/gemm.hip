@@ -25,102 +25,12 @@
 #include <type_traits>
 
 #include "gemm.h"
+#include "gemm_args.h"
+#include "gemm_f32.h"
 #include "tile.h"
 
 namespace orbit {
 namespace {
-
-struct Epi {
-  float alpha;
-  int accumulate;
-  const void* bias; int64_t sBias;
-  void* gelu_out; int64_t ldgo;
-  const void* gelu_in; int64_t ldgi;
-  const void* res; int64_t ldr, sR; int res_row_mod;
-};
-
-struct GemmKArgs {
-  const void* A; const void* B; const void* B2; void* C;
-  int M, N, K, k_split;
-  int64_t lda, ldb, ldc;
-  int64_t sA, sB, sB2, sC;
-  int batch, splits, k_per_split;
-  int vec_ok;      // N, ldc, batch strides and epilogue operands allow 16-byte access
-  float* partial;  // splits > 1: float32 partials [splits][batch][M][N]
-  float* bsum;     // column sums of B: [splits][bs_groups][batch][N] (A M-major, B N-major)
-  int bs_groups;   // tile rows that form them, each from a strided subset of the K slices
-  Epi epi;
-};
-
-template <typename T, typename OutT>
-ORBIT_DEV void epi_apply(const Epi& e, int64_t bz, int r, int c, float v, OutT* C, int64_t ldc) {
-  v *= e.alpha;
-  const int64_t off = (int64_t)r * ldc + c;
-  if (e.accumulate) v += to_f(C[off]);
-  if (e.bias) v += to_f(static_cast<const T*>(e.bias)[bz * e.sBias + c]);
-  if (e.gelu_out) {
-    static_cast<T*>(e.gelu_out)[(int64_t)r * e.ldgo + c] = from_f<T>(v);
-    v = gelu_f(v);
-  }
-  if (e.gelu_in) v *= gelu_grad_f(to_f(static_cast<const T*>(e.gelu_in)[(int64_t)r * e.ldgi + c]));
-  if (e.res) {
-    const int rr = e.res_row_mod ? r % e.res_row_mod : r;
-    v += to_f(static_cast<const T*>(e.res)[bz * e.sR + (int64_t)rr * e.ldr + c]);
-  }
-  C[off] = from_f<OutT>(v);
-}
-
-// 8 consecutive columns c0..c0+7 of row r (16-byte aligned rows)
-template <typename T> ORBIT_DEV void ld8(const T* p, float* f) {
-  unpack(ld128(p), f, (T*)nullptr);
-  if constexpr (sizeof(T) == 4) unpack(ld128(p + 4), f + 4, (T*)nullptr);
-}
-template <typename T> ORBIT_DEV void st8(T* p, const float* f) {
-  st128(p, pack(f, (T*)nullptr));
-  if constexpr (sizeof(T) == 4) st128(p + 4, pack(f + 4, (T*)nullptr));
-}
-
-// b8: the bias of columns c0..c0+7 when the caller loaded it ahead (else NULL)
-template <typename T, typename OutT>
-ORBIT_DEV void epi_apply8(const Epi& e, int64_t bz, int r, int c0, float* v, OutT* C, int64_t ldc,
-                          const float* b8 = nullptr) {
-  const int64_t off = (int64_t)r * ldc + c0;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) v[i] *= e.alpha;
-  float t[8];
-  if (e.accumulate) {
-    ld8(C + off, t);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] += t[i];
-  }
-  if (e.bias) {
-    if (b8) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) t[i] = b8[i];
-    } else {
-      ld8(static_cast<const T*>(e.bias) + bz * e.sBias + c0, t);
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] += t[i];
-  }
-  if (e.gelu_out) {
-    st8(static_cast<T*>(e.gelu_out) + (int64_t)r * e.ldgo + c0, v);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = gelu_f(v[i]);
-  }
-  if (e.gelu_in) {
-    ld8(static_cast<const T*>(e.gelu_in) + (int64_t)r * e.ldgi + c0, t);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] *= gelu_grad_f(t[i]);
-  }
-  if (e.res) {
-    const int rr = e.res_row_mod ? r % e.res_row_mod : r;
-    ld8(static_cast<const T*>(e.res) + bz * e.sR + (int64_t)rr * e.ldr + c0, t);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] += t[i];
-  }
-  st8(C + off, v);
-}
 
 // operand staging: K-major tiles (and every float32 tile) as K-contiguous LDS
 // rows; bf16 M/N-major tiles as they are, read through transposing LDS reads
@@ -693,6 +603,7 @@ constexpr TileCfg kBig{128, 128, 2, 2};
 constexpr TileCfg kNarrowN{128, 32, 4, 1};
 constexpr TileCfg kNarrowM{32, 128, 1, 4};
 constexpr TileCfg kSmall{64, 64, 2, 2};
+constexpr TileCfg kTiny{32, 32, 4, 1};   // gemm_f32_tiny (float32 only)
 
 int64_t tiles_of(const Gemm& g, const TileCfg& t) { return cdiv(g.M, t.BM) * cdiv(g.N, t.BN) * (int64_t)g.batch; }
 
@@ -757,7 +668,39 @@ Choice pick_bf16(const Gemm& g) {
   return best;
 }
 
+// float32 products. Small ones run on 32x32 tiles with the K range spread over
+// a block's waves: latency decides there, and what grows with the product is
+// the tiles' operand traffic, M N K / 4 bytes (512 x 512, K = 512: 10 us against
+// 15 on larger tiles; 512 x 2048, K = 512: 17.6 against 21; but 512 x 512,
+// K = 2048: 30 against 25). The others take 128x128 tiles and the K split with
+// the least modelled time: a round of up to 512 work items (two per CU) costs
+// 5 us + 1.36 us per 16-deep slice, one of up to 256 (one per CU) 5 + 0.80; a
+// split adds a launch and its float32 partials, written and read back (3 us
+// + 0.33 us per MB). Within 5% of the best measured split on 18 block products
+// of 1024 to 8192 rows.
+bool f32_tiny(const Gemm& g) {
+  return g.dtype == ORBIT_F32 && !g.B2 && g.K <= 1024 && (double)g.M * g.N * g.K * g.batch <= 5.5e8;
+}
+int f32_splits(const Gemm& g) {
+  const int64_t tiles = tiles_of(g, kBig), steps = cdiv(g.K, 16);
+  int best = 1;
+  double best_us = 1e300;
+  for (int sp = 1; sp <= 16; sp *= 2) {
+    if (sp > 1 && steps / sp < 8) break;
+    const int64_t items = tiles * sp, rem = items % 512;
+    const double ks = (double)cdiv(steps, sp), two = 5.0 + 1.36 * ks, one = 5.0 + 0.80 * ks;
+    double us = (double)(items / 512) * two + (rem > 256 ? two : rem > 0 ? one : 0.0);
+    if (sp > 1) us += 3.0 + 0.33 * sp * (double)g.M * g.N * g.batch * 4.0 / 1e6;
+    if (us < best_us) {
+      best_us = us;
+      best = sp;
+    }
+  }
+  return best;
+}
+
 TileCfg pick_tile(const Gemm& g) {
+  if (f32_tiny(g)) return kTiny;
   // a long reduction against a few columns (the aggregation's score product,
   // K = d = 16384 on the 113B shard): 64x64 tiles stream A ~4% faster
   if (g.N <= 32) return g.dtype == ORBIT_BF16 && g.a_kmajor && g.b_kmajor && g.K >= 8192 ? kSmall : kNarrowN;
@@ -783,6 +726,8 @@ int used_splits(const Gemm& g, int splits) {
 int pick_splits(const Gemm& g, const TileCfg& t) {
   if (g.dtype == ORBIT_BF16 && g.K >= 256 && g.M >= 128 && g.N >= 128 && t == pick_bf16(g).t)
     return pick_bf16(g).splits;
+  if (t == kTiny) return 1;
+  if (g.dtype == ORBIT_F32 && t == kBig && !g.B2) return f32_splits(g);
   const int64_t tiles = tiles_of(g, t);
   const int bke = bke_of(g.dtype);
   const int64_t ksteps = cdiv(g.K, bke);
@@ -960,7 +905,15 @@ orbit_status gemm_run(const Gemm& g, const TileCfg& t, int splits, void* ws, siz
   if (g.dtype == ORBIT_BF16) {
     return g.out_f32 ? run_typed<bf16, float>(g, a, t, s) : run_typed<bf16, bf16>(g, a, t, s);
   }
-  // float operands always produce float
+  // float operands always produce float; the split-bf16 and 32x32 kernels
+  // address their operands with 32-bit byte offsets
+  const int64_t lim = ((int64_t)1 << 31) / 4;
+  const int64_t reach = t == kTiny ? std::max<int64_t>(g.K, 32) : 128;
+  const bool near = (g.lda + 1) * reach + g.K < lim && (g.ldb + 1) * reach + g.K < lim;
+  if (!g.B2 && near && (t == kBig || t == kSmall || t == kTiny) && (g.a_kmajor || !g.b_kmajor)) {
+    ORBIT_TRY(gemm_f32_launch(t.BM, g.a_kmajor, g.b_kmajor, a, s));
+    return a.splits > 1 ? splitk_finish<float>(g, a, s) : ORBIT_OK;
+  }
   return run_typed<float, float>(g, a, t, s);
 }
 

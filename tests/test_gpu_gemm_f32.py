@@ -1,0 +1,67 @@
+"""float32 products on split bf16 matrix instructions and on 32x32 tiles: edges
+of tiles and K slices in every layout against float64, and operands holding
+infinities and NaN.
+
+The bound is the float32 one: |C - ref| <= K 2^-24 (|A| |B|) element by element
+(K sums rounded to 24 bits each; the kernels round fewer)."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+# M, N, K: below and above the 32x32-tile limit (M N K of 5.5e8, K of 1024); one past tiles
+# and slices, a single slice, K not a multiple of 16, K split over blocks, 64-wide tiles
+SHAPES = [(8, 8, 8), (40, 72, 24), (264, 136, 512), (520, 1032, 1024), (2056, 136, 2008), (1024, 1024, 1096),
+          (136, 264, 16 * 1024), (4104, 64, 2056)]
+
+
+def _operands(torch, M, N, K, ak, bk):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M * 7 + N * 3 + K)
+    A = torch.randn((M, K) if ak else (K, M), generator=g, device="cuda")
+    B = torch.randn((N, K) if bk else (K, N), generator=g, device="cuda")
+    return A, B
+
+
+def _run(lib, torch, A, B, M, N, K, ak, bk):
+    C = torch.full((M + 1, N), 7.0, device="cuda")  # a guard row behind the result
+    n = lib.orbit_gemm_workspace_bytes(0, M, N, K, ak, bk)
+    ws = torch.empty(max(n, 16), dtype=torch.uint8, device="cuda")
+    lib.orbit_gemm(0, M, N, K, A, A.shape[1], ak, B, B.shape[1], bk, C, N, 1, 1.0, None, 0, ws)
+    torch.cuda.synchronize()
+    assert bool((C[M] == 7.0).all())
+    return C[:M]
+
+
+@pytest.mark.parametrize("ak,bk", [(1, 0), (1, 1), (0, 0)])
+@pytest.mark.parametrize("M,N,K", SHAPES)
+def test_gemm_f32(lib, M, N, K, ak, bk):
+    import torch
+    A, B = _operands(torch, M, N, K, ak, bk)
+    a = (A if ak else A.t()).double()
+    b = (B.t() if bk else B).double()
+    C = _run(lib, torch, A, B, M, N, K, ak, bk)
+    worst = ((C.double() - a @ b).abs() / (a.abs() @ b.abs())).max().item()
+    assert worst <= K * 2.0 ** -24, worst
+
+
+@pytest.mark.parametrize("M,N,K", [(40, 48, 64), (1032, 1032, 1032)])
+def test_gemm_f32_not_finite(lib, M, N, K):
+    """Infinities and NaN reach exactly the outputs that float32 arithmetic gives
+    them, with the same sign; everything else stays finite and right. Values at
+    the top of the float32 range, which bf16 rounding would overflow, stay finite."""
+    import torch
+    A, B = _operands(torch, M, N, K, 1, 0)
+    B = B.abs()
+    A[3, 5], A[7, 9], A[9, 1], A[11, 2] = float("inf"), float("nan"), float("-inf"), 3.4e38
+    B[2] = 1e-3
+    a, b = A.double(), B.double()
+    C = _run(lib, torch, A, B, M, N, K, 1, 0)
+    ref = a @ b
+    ok = torch.isfinite(ref)
+    assert torch.equal(ok, torch.isfinite(C))
+    assert torch.equal(torch.isnan(ref), torch.isnan(C))
+    inf = torch.isinf(ref)
+    assert torch.equal(torch.sign(ref[inf]), torch.sign(C[inf].double()))
+    a[~torch.isfinite(a)] = 0
+    err = ((C.double() - ref).abs() / (a.abs() @ b.abs()))[ok].max().item()
+    assert err <= K * 2.0 ** -24, err
