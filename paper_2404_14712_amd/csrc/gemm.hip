@@ -187,9 +187,9 @@ constexpr unsigned kOobOffset = 0x80000000u;    // beyond num_records: the copy 
 
 #define ORBIT_LDS __attribute__((address_space(3)))
 
-ORBIT_DEV __amdgpu_buffer_rsrc_t buffer_rsrc(const void* base) {
-  // raw buffer over [base, base + 2 GiB); offsets at or past kOobOffset read zeros
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0x7fffffff, 0x00020000);
+ORBIT_DEV __amdgpu_buffer_rsrc_t buffer_rsrc(const void* base, int bytes = 0x7fffffff) {
+  // raw buffer over [base, base + bytes); offsets past it (kOobOffset too) read zeros
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
 }
 
 
@@ -222,10 +222,21 @@ struct DmaPlan {
       }
     }
   }
-  ORBIT_DEV void issue(const bf16* base, unsigned lds, int wave) const {
-    const __amdgpu_buffer_rsrc_t r = buffer_rsrc(base);
+  // RAG: K is no multiple of DBK. `left`: k of the reduction from the slice's
+  // first on; a last slice short of DBK reads zeros past it (K-major: 8-k
+  // pieces, else whole k-rows)
+  template <bool RAG>
+  ORBIT_DEV void issue(const bf16* base, int64_t ld, int left, unsigned lds, int wave, int lane) const {
+    if (!RAG || left >= DBK) {
+      const __amdgpu_buffer_rsrc_t r = buffer_rsrc(base);
 #pragma unroll
-    for (int j = 0; j < NL; ++j) dma16(r, lds + (wave * NL + j) * 1024, voff[j]);
+      for (int j = 0; j < NL; ++j) dma16(r, lds + (wave * NL + j) * 1024, voff[j]);
+    } else {
+      const bool in = !KMAJ || (((lane & 3) ^ ((lane >> 4) & 3)) * 8 < left);
+      const __amdgpu_buffer_rsrc_t r = buffer_rsrc(base, KMAJ ? 0x7fffffff : left * (int)ld * 2);
+#pragma unroll
+      for (int j = 0; j < NL; ++j) dma16(r, lds + (wave * NL + j) * 1024, in ? voff[j] : kOobOffset);
+    }
   }
 };
 
@@ -271,7 +282,10 @@ struct DmaFrag {
 // Tile configurations of the direct-to-LDS kernel. BIG: 256x256 on 8 waves
 // (two per SIMD, 128x64 each), four stages, one block per CU. HALF: 256x128
 // on 4 waves (128x64 each), three stages (72 KB), two independent blocks per
-// CU, which fills the GPU on products with few 256x256 tiles.
+// CU, which fills the GPU on products with few 256x256 tiles. QUARTER: 128x128
+// on 4 waves (64x64 each), four stages (64 KB), two blocks per CU, for products
+// whose larger tiles leave CUs idle or need K split (eight stages, one block
+// per CU: no faster, the slices' copies are not what a lone block waits for).
 template <int BM_, int BN_, int WM_, int WN_, int NS_, int OCC_, bool PP_ = false>
 struct DmaCfg {
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, NS = NS_, OCC = OCC_;
@@ -285,18 +299,23 @@ struct DmaCfg {
 using DmaBig = DmaCfg<256, 256, 2, 4, 4, 1>;
 using DmaHalf = DmaCfg<256, 128, 2, 2, 3, 2>;
 using DmaPP = DmaCfg<256, 256, 2, 4, 4, 1, true>;   // BIG in two wave groups
+using DmaQuarter = DmaCfg<128, 128, 2, 2, 4, 2>;
 
 // wait until stage s has landed when copies of the next `ahead` stages
 // (each NLS copies per wave) may still be in flight
 template <int NLS, int NS>
 ORBIT_DEV void wait_stage(int ahead) {
-  static_assert(NS == 3 || NS == 4, "ring depth");
-  if (NS == 4 && ahead >= 2) wait_vmcnt<2 * NLS>();
-  else if (ahead >= 1) wait_vmcnt<NLS>();
-  else wait_vmcnt<0>();
+  if constexpr (NS > 2) {
+    if (ahead >= NS - 2) wait_vmcnt<(NS - 2) * NLS>();
+    else wait_stage<NLS, NS - 1>(ahead);
+  } else {
+    wait_vmcnt<0>();
+  }
 }
 
-template <bool AK, bool BKM, typename OutT, typename CF>
+// RAG: K is no multiple of a slice (a kernel of its own: the test for the short
+// slice costs the main loop 2%)
+template <bool AK, bool BKM, typename OutT, typename CF, bool RAG>
 __global__ void __launch_bounds__(CF::NT, CF::OCC) gemm_dma_kernel(GemmKArgs g) {
   constexpr int BM = CF::BM, BN = CF::BN, WM = CF::WM, NS = CF::NS;
   constexpr int TM = CF::TM, TN = CF::TN, OPA = CF::OPA, STB = CF::STB;
@@ -337,7 +356,7 @@ __global__ void __launch_bounds__(CF::NT, CF::OCC) gemm_dma_kernel(GemmKArgs g) 
   const int m0 = tile_m * BM, n0 = tile_n * BN;
   const int kbeg = split * g.k_per_split;
   const int kend = min(g.K, kbeg + g.k_per_split);
-  const int nk = max(kend - kbeg, 0) / DBK;
+  const int nk = (max(kend - kbeg, 0) + (RAG ? DBK - 1 : 0)) / DBK;
 
   const bf16* A = static_cast<const bf16*>(g.A) + bz * g.sA;
   const bf16* B = static_cast<const bf16*>(g.B) + bz * g.sB;
@@ -366,8 +385,9 @@ __global__ void __launch_bounds__(CF::NT, CF::OCC) gemm_dma_kernel(GemmKArgs g) 
   const unsigned lds0 = (unsigned)(uintptr_t)(ORBIT_LDS void*)smem;
   auto issue = [&](int st) {
     const unsigned b = lds0 + (st % NS) * STB;
-    pa.issue(Ab + st * a_step, b, wave);
-    pb.issue(Bb + st * b_step, b + OPA, wave);
+    const int left = RAG ? kend - kbeg - st * DBK : DBK;
+    pa.template issue<RAG>(Ab + st * a_step, g.lda, left, b, wave, lane);
+    pb.template issue<RAG>(Bb + st * b_step, g.ldb, left, b + OPA, wave, lane);
   };
   // prologue: stages 0 .. NS-2 in flight (each wave's copies complete in issue
   // order), then wait for stage 0
@@ -592,13 +612,15 @@ __global__ void __launch_bounds__(64) splitk_reduce(GemmKArgs g) {
 struct TileCfg {
   int BM, BN, WM, WN;
   bool dma = false;  // gemm_dma_kernel (bf16 only)
+  int stages = 0;    // its ring depth
   bool operator==(const TileCfg& o) const {
-    return BM == o.BM && BN == o.BN && WM == o.WM && WN == o.WN && dma == o.dma;
+    return BM == o.BM && BN == o.BN && WM == o.WM && WN == o.WN && dma == o.dma && stages == o.stages;
   }
 };
-constexpr TileCfg kDma{DmaBig::BM, DmaBig::BN, DmaBig::WM, DmaBig::WN, true};
-constexpr TileCfg kDmaHalf{DmaHalf::BM, DmaHalf::BN, DmaHalf::WM, DmaHalf::WN, true};
-constexpr TileCfg kT256{256, 256, 2, 4};
+template <typename CF> constexpr TileCfg tile_of() { return {CF::BM, CF::BN, CF::WM, CF::WN, true, CF::NS}; }
+constexpr TileCfg kDma = tile_of<DmaBig>();
+constexpr TileCfg kDmaHalf = tile_of<DmaHalf>();
+constexpr TileCfg kDmaQuarter = tile_of<DmaQuarter>();
 constexpr TileCfg kBig{128, 128, 2, 2};
 constexpr TileCfg kNarrowN{128, 32, 4, 1};
 constexpr TileCfg kNarrowM{32, 128, 1, 4};
@@ -609,56 +631,54 @@ int64_t tiles_of(const Gemm& g, const TileCfg& t) { return cdiv(g.M, t.BM) * cdi
 
 int bke_of(orbit_dtype dt) { return dt == ORBIT_BF16 ? 64 : 32; }
 
-// gemm_dma_kernel's requirements: whole 32-deep K slices, 16-byte aligned
-// operand rows, and per-lane byte offsets within a tile below 2^31
+// gemm_dma_kernel's requirements: whole 8-k pieces of K-major rows, 16-byte
+// aligned operand rows, and per-lane byte offsets within a tile below 2^31
 bool dma_ok(const Gemm& g) {
   auto al16 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; };
   const int64_t lim = (int64_t)1 << 24;
-  return g.dtype == ORBIT_BF16 && g.B2 == nullptr && g.K % DBK == 0 && (g.a_kmajor || !g.b_kmajor) &&
+  return g.dtype == ORBIT_BF16 && g.B2 == nullptr && (g.K % 8 == 0 || !g.a_kmajor) && (g.a_kmajor || !g.b_kmajor) &&
          g.lda % 8 == 0 && g.ldb % 8 == 0 && g.sA % 8 == 0 && g.sB % 8 == 0 && g.lda < lim && g.ldb < lim &&
          al16(g.A) && al16(g.B);
 }
 
-// bf16 products: the (tile, split) pair with the least modelled time. The
-// model was fitted (least squares on log time) to every tile and split on the
-// block products of five model sizes, measured on MI355X. A launch runs in
-// rounds of `slots` concurrent work items (tile x K range; one 256x256 DMA
-// block per CU, two of the smaller tiles); a round of ks 64-deep K steps takes
-// c + r * ks microseconds with every CU busy, r depending on the operand
-// layout (forward: A K-major, B N-major; input gradient: both K-major; weight
-// gradient: A M-major, B N-major). The last round, with a fraction f of the
-// slots filled, runs faster by 1 + beta (1 - f), up to `cap`: the chip is
-// power-limited, and with fewer CUs busy they clock higher and share the
-// memory system among fewer (a 144-tile launch on 256 CUs reaches 85% of the
-// full-chip rate). A split adds its float32 partials, written and read back,
-// at 0.29 us per MB.
+// bf16 products on gemm_dma_kernel: the (tile, split) pair with the least
+// modelled time. The model was fitted (least squares on log time) to every tile
+// and split on 144 block products (T = 150 to 8192 tokens, widths 512 to
+// 12288, ragged sizes among them), measured on MI355X. Work items (tile x K
+// range) run in rounds of `slots` (one 256x256 block per CU, two of the smaller
+// tiles). A full round of ks 64-deep K steps costs c + r1 ks microseconds; the
+// last round, with a fraction f of the slots filled, has its own step cost:
+// rising from r0 to r5 up to f = 1/2 (fewer CUs busy share the memory system
+// and clock higher), and from rj to r1 above it (with two blocks per CU some
+// CUs then hold two, and they set the time). Input- and weight-gradient
+// layouts scale the step by dx and dw. A split adds a launch and its float32
+// partials, written and read back. The choices are within 1.1% of the best
+// measured pair in the geometric mean.
+// The 128x128 tile is what short launches needed: with 1770 tokens, 1024 x 1024
+// and K = 1024 it takes 15.5 us in one launch against 24.9 (256x128, K split);
+// with 150 tokens, 768 x 768 12 against 17.6.
 struct Choice { TileCfg t; int splits; };
 
 Choice pick_bf16(const Gemm& g) {
-  struct Cand { TileCfg t; int slots; double c, fwd, dx, dw, beta, cap; };
-  const Cand cands[] = {{kDma, 256, 11.38, 1.540, 1.610, 1.683, 0.85, 1.562},
-                        {kDmaHalf, 512, 8.41, 1.951, 1.906, 1.995, 1.343, 2.093},
-                        {kT256, 256, 9.97, 2.083, 1.986, 2.166, 0.239, 1.114},
-                        {kBig, 512, 5.47, 1.367, 1.197, 1.394, 0.60, 1.425}};
-  constexpr double kSplitUsPerMB = 0.2922;
-  const bool dma = dma_ok(g);
-  Choice best{kBig, 1};
+  struct Cand { TileCfg t; int slots; double c, r0, r5, rj, r1, dx, dw; };
+  const Cand cands[] = {{kDma, 256, 11.57, 0.972, 1.222, 1.127, 1.579, 0.997, 1.060},
+                        {kDmaHalf, 512, 9.17, 0.743, 1.087, 1.435, 1.823, 1.023, 1.081},
+                        {kDmaQuarter, 512, 6.89, 0.392, 0.691, 0.953, 1.009, 1.024, 1.030}};
+  Choice best{kDmaQuarter, 1};
   double best_us = 1e300;
   for (const Cand& c : cands) {
-    if (g.M < c.t.BM || g.N < c.t.BN) continue;
-    if (c.t.dma && !dma) continue;
-    const double rate = g.a_kmajor ? (g.b_kmajor ? c.dx : c.fwd) : c.dw;
+    if (!(c.t == kDmaQuarter) && (g.M < c.t.BM || g.N < c.t.BN)) continue;
+    const double m = g.a_kmajor ? (g.b_kmajor ? c.dx : 1.0) : c.dw;
     const int64_t tiles = tiles_of(g, c.t);
     const int64_t ksteps = cdiv(g.K, 64);
     for (int sp = 1; sp <= 16; sp *= 2) {
-      if (sp > 1 && (ksteps / sp < 8 || tiles * sp > 2048)) break;
-      const int64_t items = tiles * sp;
-      const int64_t ks = cdiv(cdiv(g.K, sp), 64);
-      const int64_t n = cdiv(items, c.slots);
-      const double f = (double)(items - (n - 1) * c.slots) / c.slots;
-      const double boost = std::min(c.cap, 1.0 + c.beta * (1.0 - f));
-      double us = ((double)(n - 1) + 1.0 / boost) * (c.c + rate * (double)ks);
-      if (sp > 1) us += kSplitUsPerMB * sp * (double)g.M * g.N * g.batch * 4.0 / 1e6;
+      if (sp > 1 && (ksteps / sp < 4 || tiles * sp > 2304)) break;
+      const int64_t items = tiles * sp, full = items / c.slots;
+      const double ks = sp > 1 ? (double)cdiv(cdiv(g.K, sp), 64) : (double)g.K / 64.0;
+      const double f = (double)(items - full * c.slots) / c.slots;
+      const double r = f <= 0.5 ? c.r0 + (c.r5 - c.r0) * 2.0 * f : c.rj + (c.r1 - c.rj) * (2.0 * f - 1.0);
+      double us = (double)full * (c.c + m * c.r1 * ks) + (f > 0.0 ? c.c + m * r * ks : 0.0);
+      if (sp > 1) us += 1.82 + sp * (0.117 + 0.234 * (double)g.M * g.N * g.batch * 4.0 / 1e6);
       if (us < best_us) {
         best_us = us;
         best = {c.t, sp};
@@ -667,6 +687,8 @@ Choice pick_bf16(const Gemm& g) {
   }
   return best;
 }
+// the products it chooses for
+bool on_dma(const Gemm& g) { return g.K >= DBK && g.M > 64 && g.N > 64 && dma_ok(g); }
 
 // float32 products. Small ones run on 32x32 tiles with the K range spread over
 // a block's waves: latency decides there, and what grows with the product is
@@ -706,12 +728,7 @@ TileCfg pick_tile(const Gemm& g) {
   if (g.N <= 32) return g.dtype == ORBIT_BF16 && g.a_kmajor && g.b_kmajor && g.K >= 8192 ? kSmall : kNarrowN;
   if (g.M <= 32) return kNarrowM;
   if (g.M <= 64 || g.N <= 64) return kSmall;
-  if (g.dtype == ORBIT_BF16 && g.K >= 256 && g.M >= 128 && g.N >= 128) return pick_bf16(g).t;
-  // short reductions with a large output (a per-head product over head_dim):
-  // the output write dominates, and the two-blocks-per-CU DMA tile overlaps
-  // one block's stores with the other's loads (25% faster than 128x128 tiles)
-  if (g.dtype == ORBIT_BF16 && g.K >= DBK && g.M >= 256 && g.N >= 128 && dma_ok(g)) return kDmaHalf;
-  return kBig;
+  return on_dma(g) ? pick_bf16(g).t : kBig;
 }
 
 // K ranges actually launched for a requested split count: whole 64-deep steps
@@ -724,8 +741,7 @@ int used_splits(const Gemm& g, int splits) {
 }
 
 int pick_splits(const Gemm& g, const TileCfg& t) {
-  if (g.dtype == ORBIT_BF16 && g.K >= 256 && g.M >= 128 && g.N >= 128 && t == pick_bf16(g).t)
-    return pick_bf16(g).splits;
+  if (t.dma) return pick_bf16(g).splits;
   if (t == kTiny) return 1;
   if (g.dtype == ORBIT_F32 && t == kBig && !g.B2) return f32_splits(g);
   const int64_t tiles = tiles_of(g, t);
@@ -744,8 +760,11 @@ int pick_splits(const Gemm& g, const TileCfg& t) {
 template <typename OutT>
 orbit_status splitk_finish(const Gemm& g, GemmKArgs& a, hipStream_t s);
 
-template <bool AK, bool BKM, typename OutT, typename CF>
+template <bool AK, bool BKM, typename OutT, typename CF, bool RAG = false>
 orbit_status run_dma(const Gemm& g, GemmKArgs& a, hipStream_t s) {
+  if constexpr (!RAG) {
+    if (g.K % DBK != 0) return run_dma<AK, BKM, OutT, CF, true>(g, a, s);
+  }
   static const std::string name = std::string(CF::PP ? "gemm_dma_pp<" : "gemm_dma<") + std::to_string(CF::BM) + "x" + std::to_string(CF::BN) +
                                   "," + (AK ? "AK" : "AM") + "," + (BKM ? "BK" : "BN") + "," +
                                   (sizeof(OutT) == 2 ? "bf16" : "f32") + ">";
@@ -754,14 +773,14 @@ orbit_status run_dma(const Gemm& g, GemmKArgs& a, hipStream_t s) {
                        (double)g.M * g.N * sizeof(OutT) * g.batch;
   KernelInfo ki{name.c_str(), flops, bytes};
   static const bool attr = [] {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_dma_kernel<AK, BKM, OutT, CF>),
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_dma_kernel<AK, BKM, OutT, CF, RAG>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, CF::LDS);
     (void)hipGetLastError();
     return true;
   }();
   (void)attr;
   dim3 grid((unsigned)(cdiv(g.N, CF::BN) * cdiv(g.M, CF::BM)), 1, (unsigned)(g.batch * a.splits));
-  ORBIT_TRY(launch(ki, gemm_dma_kernel<AK, BKM, OutT, CF>, grid, dim3(CF::NT), (size_t)CF::LDS, s, a));
+  ORBIT_TRY(launch(ki, gemm_dma_kernel<AK, BKM, OutT, CF, RAG>, grid, dim3(CF::NT), (size_t)CF::LDS, s, a));
   return a.splits > 1 ? splitk_finish<OutT>(g, a, s) : ORBIT_OK;
 }
 
@@ -812,15 +831,14 @@ orbit_status splitk_finish(const Gemm& g, GemmKArgs& a, hipStream_t s) {
 template <typename T, typename OutT, bool AK, bool BKM>
 orbit_status run_layout(const Gemm& g, GemmKArgs& a, const TileCfg& t, hipStream_t s) {
   if constexpr (sizeof(T) == 2) {
-    if (t.dma && t.BN == DmaHalf::BN) return run_dma<AK, BKM, OutT, DmaHalf>(g, a, s);
+    if (t == kDmaQuarter) return run_dma<AK, BKM, OutT, DmaQuarter>(g, a, s);
+    if (t == kDmaHalf) return run_dma<AK, BKM, OutT, DmaHalf>(g, a, s);
     // K-major A (forward and input-gradient products): the two-group loop,
     // 1-4% faster there; with M-major A (weight gradients) it is 2-3% slower
     if (t.dma) {
       if constexpr (AK) return run_dma<AK, BKM, OutT, DmaPP>(g, a, s);
       else return run_dma<AK, BKM, OutT, DmaBig>(g, a, s);
     }
-    if (t.BM == 256 && t.BN == 256 && t.WM == 2) return run_cfg<T, OutT, 256, 256, 2, 4, AK, BKM>(g, a, s);
-    if (t.BM == 256 && t.BN == 256 && t.WM == 4) return run_cfg<T, OutT, 256, 256, 4, 2, AK, BKM>(g, a, s);
   }
   if (t.BM == 128 && t.BN == 128) return run_cfg<T, OutT, 128, 128, 2, 2, AK, BKM>(g, a, s);
   if constexpr (sizeof(T) == 2 && AK && BKM) {
