@@ -198,8 +198,12 @@ ORBIT_DEV __amdgpu_buffer_rsrc_t buffer_rsrc(const void* base, int bytes = 0x7ff
 //    logical chunk c sits at physical chunk c ^ ((r >> 2) & 3). A 1 KB copy
 //    covers 16 rows.
 //  M/N-major source X[k*ld + row]: LDS k-row kr holds 2 ROWS bytes (ROWS / 8
-//    chunks of 8 rows); logical chunk c sits at physical chunk c ^ (4 (kr & 3)).
+//    chunks of 8 rows); logical chunk c sits at physical chunk c ^ (4 (kr & 3)),
+//    of 64 rows, two of whose k-rows span the banks, at c ^ (2 (kr & 2)).
 //    A 1 KB copy covers 512 / ROWS k-rows.
+template <int ROWS>
+ORBIT_DEV int mn_swizzle(int kr) { return ROWS == 64 ? 2 * (kr & 2) : 4 * (kr & 3); }
+
 template <bool KMAJ, int ROWS, int NW>
 struct DmaPlan {
   static constexpr int BYTES = ROWS * DBK * 2;
@@ -217,7 +221,7 @@ struct DmaPlan {
       } else {
         constexpr int CPR = ROWS / 8, KPB = 64 / CPR;
         const int kr = blk * KPB + lane / CPR;
-        const int c = (lane % CPR) ^ (4 * (kr & 3));
+        const int c = (lane % CPR) ^ mn_swizzle<ROWS>(kr);
         voff[j] = (row0 + c * 8 < rlim) ? (unsigned)(kr * ld * 2 + c * 16) : kOobOffset;
       }
     }
@@ -233,7 +237,12 @@ struct DmaPlan {
       for (int j = 0; j < NL; ++j) dma16(r, lds + (wave * NL + j) * 1024, voff[j]);
     } else {
       const bool in = !KMAJ || (((lane & 3) ^ ((lane >> 4) & 3)) * 8 < left);
-      const __amdgpu_buffer_rsrc_t r = buffer_rsrc(base, KMAJ ? 0x7fffffff : left * (int)ld * 2);
+      // the address is wave-uniform, which the compiler no longer sees here
+      const uint64_t p = reinterpret_cast<uint64_t>(base);
+      const uint64_t u = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p) |
+                         (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(p >> 32)) << 32;
+      const __amdgpu_buffer_rsrc_t r =
+          buffer_rsrc(reinterpret_cast<const void*>(u), KMAJ ? 0x7fffffff : __builtin_amdgcn_readfirstlane(left * (int)ld * 2));
 #pragma unroll
       for (int j = 0; j < NL; ++j) dma16(r, lds + (wave * NL + j) * 1024, in ? voff[j] : kOobOffset);
     }
@@ -257,7 +266,7 @@ struct DmaFrag {
       // +4) at rows 16 (G & 1) + 4 (q & 3) .. +3; lane 16 G + i receives row
       // 16 (G & 1) + i at those k
       const int G = lane >> 4, q = lane & 15;
-      const int xs = 4 * ((q >> 2) & 3);
+      const int xs = mn_swizzle<ROWS>(q >> 2);
       const int cb = 2 * (G & 1) + ((q & 3) >> 1);
 #pragma unroll
       for (int i = 0; i < NF; ++i) {
@@ -286,6 +295,7 @@ struct DmaFrag {
 // on 4 waves (64x64 each), four stages (64 KB), two blocks per CU, for products
 // whose larger tiles leave CUs idle or need K split (eight stages, one block
 // per CU: no faster, the slices' copies are not what a lone block waits for).
+// THIN: 128x64, for products of 33 to 64 columns (per-head products).
 template <int BM_, int BN_, int WM_, int WN_, int NS_, int OCC_, bool PP_ = false>
 struct DmaCfg {
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, NS = NS_, OCC = OCC_;
@@ -300,6 +310,7 @@ using DmaBig = DmaCfg<256, 256, 2, 4, 4, 1>;
 using DmaHalf = DmaCfg<256, 128, 2, 2, 3, 2>;
 using DmaPP = DmaCfg<256, 256, 2, 4, 4, 1, true>;   // BIG in two wave groups
 using DmaQuarter = DmaCfg<128, 128, 2, 2, 4, 2>;
+using DmaThin = DmaCfg<128, 64, 4, 1, 4, 3>;
 
 // wait until stage s has landed when copies of the next `ahead` stages
 // (each NLS copies per wave) may still be in flight
@@ -621,6 +632,7 @@ template <typename CF> constexpr TileCfg tile_of() { return {CF::BM, CF::BN, CF:
 constexpr TileCfg kDma = tile_of<DmaBig>();
 constexpr TileCfg kDmaHalf = tile_of<DmaHalf>();
 constexpr TileCfg kDmaQuarter = tile_of<DmaQuarter>();
+constexpr TileCfg kDmaThin = tile_of<DmaThin>();
 constexpr TileCfg kBig{128, 128, 2, 2};
 constexpr TileCfg kNarrowN{128, 32, 4, 1};
 constexpr TileCfg kNarrowM{32, 128, 1, 4};
@@ -727,7 +739,11 @@ TileCfg pick_tile(const Gemm& g) {
   // K = d = 16384 on the 113B shard): 64x64 tiles stream A ~4% faster
   if (g.N <= 32) return g.dtype == ORBIT_BF16 && g.a_kmajor && g.b_kmajor && g.K >= 8192 ? kSmall : kNarrowN;
   if (g.M <= 32) return kNarrowM;
-  if (g.M <= 64 || g.N <= 64) return kSmall;
+  // 33 to 64 columns (the aggregation's per-head value products): the 128x64
+  // DMA tile, 8192 patches x 1024 x 16 heads of 64: 103 -> 82 us forward, 89 ->
+  // 85 weight gradient against 64x64 tiles; 700 patches: 191 -> 177 us for the
+  // whole aggregation (no K split and no reduction)
+  if (g.M <= 64 || g.N <= 64) return g.N > 32 && g.M >= 128 && g.K >= DBK && dma_ok(g) ? kDmaThin : kSmall;
   return on_dma(g) ? pick_bf16(g).t : kBig;
 }
 
@@ -741,6 +757,11 @@ int used_splits(const Gemm& g, int splits) {
 }
 
 int pick_splits(const Gemm& g, const TileCfg& t) {
+  if (t == kDmaThin) {
+    // as many K ranges as give half the CUs a block
+    const int64_t tiles = tiles_of(g, t), most = cdiv(g.K, 512);
+    return (int)std::max<int64_t>(1, std::min<int64_t>(cdiv(128, tiles), std::min<int64_t>(most, 16)));
+  }
   if (t.dma) return pick_bf16(g).splits;
   if (t == kTiny) return 1;
   if (g.dtype == ORBIT_F32 && t == kBig && !g.B2) return f32_splits(g);
@@ -831,6 +852,7 @@ orbit_status splitk_finish(const Gemm& g, GemmKArgs& a, hipStream_t s) {
 template <typename T, typename OutT, bool AK, bool BKM>
 orbit_status run_layout(const Gemm& g, GemmKArgs& a, const TileCfg& t, hipStream_t s) {
   if constexpr (sizeof(T) == 2) {
+    if (t == kDmaThin) return run_dma<AK, BKM, OutT, DmaThin>(g, a, s);
     if (t == kDmaQuarter) return run_dma<AK, BKM, OutT, DmaQuarter>(g, a, s);
     if (t == kDmaHalf) return run_dma<AK, BKM, OutT, DmaHalf>(g, a, s);
     // K-major A (forward and input-gradient products): the two-group loop,

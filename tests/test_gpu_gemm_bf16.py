@@ -1,4 +1,4 @@
-"""bf16 products at the edges of the 128x128 tile and of its 32-deep K slices
+"""bf16 products at the edges of the 128x128 and 128x64 tiles and of their 32-deep K slices
 (short last slices in both operand layouts, split K with a short last range),
 against float64.
 
@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 # M, N, K: one past tiles; K of one short slice, of a multiple plus 8, 16 and 24; products whose
 # cost model picks 128, 256x128 and 256x256 tiles with such K
 SHAPES = [(72, 72, 32), (136, 264, 40), (264, 136, 1000), (152, 768, 2312), (1032, 1048, 1048), (1768, 1024, 1784),
-          (4104, 4096, 1064), (520, 6152, 4120)]
+          (4104, 4096, 1064), (520, 6152, 4120),
+          (136, 64, 1032), (1032, 40, 520)]
 
 
 @pytest.mark.parametrize("ak,bk", [(1, 0), (1, 1), (0, 0)])
