@@ -11,6 +11,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "attention_f32.h"
 #include "kernels.h"
 #include "tile.h"
 
@@ -1537,6 +1538,17 @@ size_t attn_bwd_base_bytes(int B, int H, int L, int dh) {
   return align_up((size_t)B * H * (L + 2 * dh) * sizeof(float)) + 2 * colsum_part_bytes(L, H * dh, false, B);
 }
 
+// float32: the 32-row blocks of attention_f32.hip where the general kernels'
+// 128-row blocks are few. With 128 of those (head_dim 64) the three kernels
+// take 233 against 349 us, with 256 408 against 358: theirs grow with the grid,
+// the general ones' do not below one block per CU. They address a (sample,
+// head) slice with 32-bit byte offsets, up to 160 rows past its end; wider
+// slices stay on the general kernels.
+bool f32_small(const AttnIO& io, int64_t lddo) {
+  const int64_t ld = std::max(std::max(io.ldq, io.ldk), std::max(io.ldv, lddo));
+  return cdiv(io.L, 128) * (int64_t)io.H * io.B < 192 && (io.L + 160) * ld * 4 < (int64_t)1 << 31;
+}
+
 template <typename T, int DH>
 orbit_status fwd_t(const AttnIO& io, void* o, int64_t ldo, float* lse, float* o32, int64_t ldo32, void* scratch,
                    size_t scratch_bytes, hipStream_t s) {
@@ -1562,7 +1574,17 @@ orbit_status fwd_t(const AttnIO& io, void* o, int64_t ldo, float* lse, float* o3
     }
     return launch(ki, attn_fwd_tr<DH>, dim3((unsigned)cdiv(io.L, 128), io.H, io.B), dim3(256), 0, s, a);
   }
-  return launch(ki, attn_fwd_kernel<T, DH>, dim3((unsigned)cdiv(io.L, 128), io.H, io.B), dim3(256), 0, s, a);
+  if constexpr (sizeof(T) == 4) {
+    if (f32_small(io, 0)) {
+      AttnF32Args x{};
+      x.q = static_cast<const float*>(io.q); x.k = static_cast<const float*>(io.k); x.v = static_cast<const float*>(io.v);
+      x.ldq = io.ldq; x.ldk = io.ldk; x.ldv = io.ldv;
+      x.o = static_cast<float*>(o); x.ldo = ldo; x.o32 = o32; x.ldo32 = ldo32; x.lse_out = lse;
+      x.H = io.H; x.L = io.L; x.sl2 = a.sl2;
+      return attn_f32_forward(x, io.B, DH, s);
+    }
+    return launch(ki, attn_fwd_kernel<T, DH>, dim3((unsigned)cdiv(io.L, 128), io.H, io.B), dim3(256), 0, s, a);
+  }
 }
 
 template <typename T, int DH>
@@ -1602,6 +1624,18 @@ orbit_status bwd_t(const AttnIO& io, const void* o, int64_t ldo, int o_f32, cons
   }
   BwdArgs a{io.q, io.k, io.v, dO, lse, D, qsum, ksum, dq, dk, dv, io.ldq, io.ldk, io.ldv, lddo, ldg, io.H, io.L,
             kLog2e / sqrtf((float)DH), 1.f / sqrtf((float)DH)};
+  if constexpr (sizeof(T) == 4) {
+    if (f32_small(io, lddo)) {
+      AttnF32Args x{};
+      x.q = static_cast<const float*>(io.q); x.k = static_cast<const float*>(io.k); x.v = static_cast<const float*>(io.v);
+      x.dO = static_cast<const float*>(dO);
+      x.ldq = io.ldq; x.ldk = io.ldk; x.ldv = io.ldv; x.lddo = lddo;
+      x.lse = lse; x.D = D; x.qsum = qsum; x.ksum = ksum;
+      x.dq = static_cast<float*>(dq); x.dk = static_cast<float*>(dk); x.dv = static_cast<float*>(dv); x.ldg = ldg;
+      x.H = io.H; x.L = io.L; x.sl2 = a.sl2; x.scale = a.scale;
+      return attn_f32_backward(x, io.B, DH, s);
+    }
+  }
   const int ns = sizeof(T) == 2 ? attn_splits(io.B, io.H, io.L) : 1;
   if (ns > 1) {
     a.B = io.B;
