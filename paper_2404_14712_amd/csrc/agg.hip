@@ -128,17 +128,11 @@ __global__ void __launch_bounds__(256) agg_gemv_final(const float* __restrict__ 
 // and lane h adds the dh / 8 chunks of head h in order. A row is taken in
 // passes of whole heads, at most kFoldMaxChunks chunks each.
 constexpr int kFoldMaxChunks = 1024;
-// Block 0 also keeps a copy of b_v (16-byte pieces): the streaming backward
-// takes it off the stored value outputs.
 template <typename T>
 __global__ void __launch_bounds__(256) agg_fold_key(const T* __restrict__ wk, const float* __restrict__ q,
-                                                    T* __restrict__ Ut, const T* __restrict__ bv, T* __restrict__ bv_out,
-                                                    int d, int H, int dh) {
+                                                    T* __restrict__ Ut, int d, int H, int dh) {
   __shared__ float part[4][kFoldMaxChunks];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  if (blockIdx.x == 0 && bv_out)
-    for (int j = threadIdx.x; j < H * dh * (int)sizeof(T) / 16; j += 256)
-      st128(reinterpret_cast<char*>(bv_out) + j * 16, ld128(reinterpret_cast<const char*>(bv) + j * 16));
   const int i = blockIdx.x * 4 + wave;
   const int per = dh / 8, hp = kFoldMaxChunks / per;  // chunks per head, heads per pass
   const T* row = wk + (int64_t)i * H * dh;
@@ -637,9 +631,9 @@ Sizes sizes(const orbit_agg_desc& a) {
 size_t esz(orbit_dtype dt) { return dt == ORBIT_BF16 ? 2 : 4; }
 
 // saved layout: q f32 [A] | Ut [H, d] | a32 [T, H, V] ([T, V, H] on the streaming path) | xbar [T, H, d]
-//               | zh [T, A] | b_v [A] (streaming path)
+//               | zh [T, A] | zh - b_v [T, A] (streaming path)
 struct Saved {
-  float* q; void* Ut; float* a32; void* xbar; void* zh; void* bv;
+  float* q; void* Ut; float* a32; void* xbar; void* zh; void* vh;
 };
 Saved carve_saved(const Sizes& z, orbit_dtype dt, void* base, size_t* used) {
   Carver c(base);
@@ -649,7 +643,7 @@ Saved carve_saved(const Sizes& z, orbit_dtype dt, void* base, size_t* used) {
   s.a32 = c.take<float>((size_t)z.T * z.H * z.V);
   s.xbar = c.take<char>((size_t)z.T * z.H * z.d * esz(dt));
   s.zh = c.take<char>((size_t)z.T * z.A * esz(dt));
-  s.bv = agg_stream_ok(dt, z.V, z.d, z.H) ? c.take<char>((size_t)z.A * esz(dt)) : nullptr;
+  s.vh = agg_stream_ok(dt, z.V, z.d, z.H) ? c.take<char>((size_t)z.T * z.A * esz(dt)) : nullptr;
   if (used) *used = c.used();
   return s;
 }
@@ -765,12 +759,11 @@ orbit_status agg_forward(const orbit_agg_desc& a, const void* tok, const orbit_a
   if (dt == ORBIT_BF16) {
     ORBIT_TRY((gemv_cols<bf16, false>("agg_query", p.w_q, p.q0, nullptr, p.b_q, sv.q, gvp, z.d, z.A, z.H, z.dh, s)));
     ORBIT_TRY(launch(ku, agg_fold_key<bf16>, dim3((unsigned)cdiv(z.d, 4)), dim3(256), 0, s, (const bf16*)p.w_k,
-                     (const float*)sv.q, (bf16*)sv.Ut, (const bf16*)p.b_v, (bf16*)sv.bv, z.d, z.H, z.dh));
+                     (const float*)sv.q, (bf16*)sv.Ut, z.d, z.H, z.dh));
   } else {
     ORBIT_TRY((gemv_cols<float, false>("agg_query", p.w_q, p.q0, nullptr, p.b_q, sv.q, gvp, z.d, z.A, z.H, z.dh, s)));
     ORBIT_TRY(launch(ku, agg_fold_key<float>, dim3((unsigned)cdiv(z.d, 4)), dim3(256), 0, s,
-                     (const float*)p.w_k, (const float*)sv.q, (float*)sv.Ut, (const float*)nullptr,
-                     (float*)nullptr, z.d, z.H, z.dh));
+                     (const float*)p.w_k, (const float*)sv.q, (float*)sv.Ut, z.d, z.H, z.dh));
   }
   if (agg_stream_ok(dt, z.V, z.d, z.H)) {
     // 2.-4. in one pass over the tokens
@@ -829,6 +822,9 @@ orbit_status agg_forward(const orbit_agg_desc& a, const void* tok, const orbit_a
     g.B = p.w_v; g.ldb = z.A; g.b_kmajor = false; g.sB = z.dh;
     g.C = sv.zh; g.ldc = z.A; g.sC = z.dh;
     g.bias = p.b_v; g.sBias = z.dh;
+    // the streaming backward's row sums come from the outputs before the bias:
+    // a bias larger than they are would leave few of their bits in zh
+    g.raw_out = sv.vh; g.ldraw = z.A; g.sRaw = z.dh;
     g.M = (int)z.T; g.N = z.dh; g.K = z.d; g.batch = z.H;
     ORBIT_TRY(gemm(g, gws, gws_bytes, s));
   }
@@ -946,9 +942,8 @@ orbit_status agg_backward(const orbit_agg_desc& a, const void* tok, const orbit_
     ORBIT_TRY(gemm(g, gws, gws_bytes, s));
   }
   if (stream) {
-    const bf16* zh = static_cast<const bf16*>(sv.zh);
-    ORBIT_TRY(agg_stream_rowsum(zh, static_cast<const bf16*>(dzh), static_cast<const bf16*>(sv.bv), rowsum, z.T, z.H,
-                                z.dh, s));
+    ORBIT_TRY(agg_stream_rowsum(static_cast<const bf16*>(sv.vh), static_cast<const bf16*>(dzh), rowsum, z.T, z.H, z.dh,
+                                s));
     ORBIT_TRY(agg_stream_bwd(static_cast<const bf16*>(tok), static_cast<const bf16*>(dxbar),
                              static_cast<const bf16*>(sv.Ut), sv.a32, rowsum, static_cast<const bf16*>(sv.xbar),
                              static_cast<bf16*>(dtok), du_part, dU, z.T, z.V, z.d, z.H, scale, s));

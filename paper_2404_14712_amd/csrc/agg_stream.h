@@ -20,9 +20,8 @@ orbit_status agg_stream_fwd(const bf16* tok, const bf16* Ut, float* a32, bf16* x
                             float scale, hipStream_t s);
 
 // cp[t][16]: the softmax backward's row sums c_h = sum_v a_v (x_v . dxbar_h)
-// from the stored value outputs, (zh_h - b_v^h) . dzh_h
-orbit_status agg_stream_rowsum(const bf16* zh, const bf16* dzh, const bf16* bv, float* cp, int64_t T, int H, int dh,
-                               hipStream_t s);
+// from the stored value outputs before their bias, vh_h . dzh_h
+orbit_status agg_stream_rowsum(const bf16* vh, const bf16* dzh, float* cp, int64_t T, int H, int dh, hipStream_t s);
 
 // dA, softmax backward, dtok and the partials of dU in one pass; dU [d, H]
 // float32 is finished from the partials

@@ -12,9 +12,11 @@
 //             dU += dS^T X
 //
 // c_h = sum_v a_v dA_v couples the rows of a patch. It equals xbar_h . dxbar_h
-// = (zh_h - b_v^h) . dzh_h, which is known before the pass, up to the bf16
-// rounding of zh. The pass sums the exact c alongside, and what the rounding
-// did to dU, (c' - c) scale xbar_h, is added at the patch's end.
+// = vh_h . dzh_h (vh: the value outputs before their bias, stored by the
+// forward; zh - b_v would lose their bits to a large bias), which is known
+// before the pass, up to the bf16 rounding of vh and dxbar. The pass sums the
+// exact c alongside, and what the rounding did to dU, (c' - c) scale xbar_h, is
+// added at the patch's end.
 //
 // Eight waves share a block; wave w owns columns [w CPW, (w + 1) CPW) of every
 // row. Rows arrive in slots of 16 variables x DP = 8 CPW columns, copied by the
@@ -302,10 +304,9 @@ __global__ void __launch_bounds__(kThreads, 2 * C::BPC) agg_stream_fwd_kernel(co
 // ---------------------------------------------------------------------------
 // backward
 // ---------------------------------------------------------------------------
-// (zh_h - b_v^h) . dzh_h per (token, head): 8 lanes each
-__global__ void __launch_bounds__(256) agg_stream_rowsum_kernel(const bf16* __restrict__ zh,
-                                                                const bf16* __restrict__ dzh,
-                                                                const bf16* __restrict__ bv, float* __restrict__ cp,
+// vh_h . dzh_h per (token, head): 8 lanes each
+__global__ void __launch_bounds__(256) agg_stream_rowsum_kernel(const bf16* __restrict__ vh,
+                                                                const bf16* __restrict__ dzh, float* __restrict__ cp,
                                                                 int64_t n, int H, int dh) {
   const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 3;
   const int sub = threadIdx.x & 7;
@@ -315,12 +316,11 @@ __global__ void __launch_bounds__(256) agg_stream_rowsum_kernel(const bf16* __re
   const int64_t off = t * H * dh + (int64_t)h * dh;
   float s = 0.f;
   for (int j = sub * 8; j < dh; j += 64) {
-    float z[8], g[8], b[8];
-    unpack(ld128(zh + off + j), z, (bf16*)nullptr);
+    float z[8], g[8];
+    unpack(ld128(vh + off + j), z, (bf16*)nullptr);
     unpack(ld128(dzh + off + j), g, (bf16*)nullptr);
-    unpack(ld128(bv + (int64_t)h * dh + j), b, (bf16*)nullptr);
 #pragma unroll
-    for (int u = 0; u < 8; ++u) s += (z[u] - b[u]) * g[u];
+    for (int u = 0; u < 8; ++u) s += z[u] * g[u];
   }
 #pragma unroll
   for (int o = 1; o < 8; o <<= 1) s += __shfl_xor(s, o, 64);
@@ -651,11 +651,9 @@ orbit_status agg_stream_fwd(const bf16* tok, const bf16* Ut, float* a32, bf16* x
   }
 }
 
-orbit_status agg_stream_rowsum(const bf16* zh, const bf16* dzh, const bf16* bv, float* cp, int64_t T, int H, int dh,
-                               hipStream_t s) {
+orbit_status agg_stream_rowsum(const bf16* vh, const bf16* dzh, float* cp, int64_t T, int H, int dh, hipStream_t s) {
   KernelInfo k{"agg_stream_rowsum", 0.0, (double)T * H * dh * 4.0};
-  return launch(k, agg_stream_rowsum_kernel, dim3((unsigned)cdiv(T * H, 32)), dim3(256), 0, s, zh, dzh, bv, cp, T * H, H,
-                dh);
+  return launch(k, agg_stream_rowsum_kernel, dim3((unsigned)cdiv(T * H, 32)), dim3(256), 0, s, vh, dzh, cp, T * H, H, dh);
 }
 
 orbit_status agg_stream_bwd(const bf16* tok, const bf16* dxbar, const bf16* Ut, const float* a32, const float* cp,

@@ -59,3 +59,31 @@ def test_agg_stream(lib, case):
     assert bool((dtok[-1] == 7.0).all())
     for k in rg:
         check(f"d{k}", host(g[k]), rg[k], tol, floor_ref=rg["b_q"])
+
+
+@pytest.mark.parametrize("V", [2, 40])
+def test_agg_stream_large_value_bias(lib, V):
+    """A value bias far above the value outputs: the token gradient does not see
+    it (the weights sum to one), so the bound is the usual one."""
+    import torch
+    from paper_2404_14712_amd._lib import AggDesc
+    B, L, d, H, dh = 1, 24, 512, 8, 64
+    c = synth.small_config("115m", dtype="bf16", B=B, L=L, V=V, d=d, agg_heads=H, agg_head_dim=dh, sigma=0.1)
+    tok = synth.normal(c.seed, "tok", (B, L, V, d), dtype="bf16")
+    prm = synth.make_params(c.seed, "agg", synth.agg_param_shapes(d, H * dh, L), 0.1, "bf16")
+    prm["b_v"] = np.full_like(prm["b_v"], 4096.0) * np.sign(prm["b_v"])
+    dz = synth.normal(c.seed, "dz", (B, L, d), dtype="bf16")
+    desc = AggDesc(B, L, V, d, H, dh, 1)
+    pd = {k: dev(v, "bf16") for k, v in prm.items()}
+    tokd, dzd = dev(tok, "bf16"), dev(dz, "bf16")
+    z = torch.zeros(B, L, d, dtype=torch.bfloat16, device="cuda")
+    saved = torch.full((lib.orbit_var_aggregate_saved_bytes(desc),), 255, dtype=torch.uint8, device="cuda")
+    ws = torch.full((lib.orbit_var_aggregate_workspace_bytes(desc),), 255, dtype=torch.uint8, device="cuda")
+    dtok = torch.zeros(B * L * V, d, dtype=torch.bfloat16, device="cuda")
+    g = {k: torch.zeros(v.shape, dtype=torch.float32, device="cuda") for k, v in prm.items()}
+    lib.orbit_var_aggregate(desc, tokd, pd, z, saved, ws)
+    lib.orbit_var_aggregate_bwd(desc, tokd, pd, saved, dzd, dtok, g, 0, ws)
+    torch.cuda.synchronize()
+    _, cache = O.agg_fwd(tok, prm, H)
+    rdtok, _ = O.agg_bwd(dz, cache, prm)
+    check("dtok", host(dtok).reshape(rdtok.shape), rdtok, TOL["bf16"])
