@@ -630,10 +630,9 @@ Sizes sizes(const orbit_agg_desc& a) {
 }
 size_t esz(orbit_dtype dt) { return dt == ORBIT_BF16 ? 2 : 4; }
 
-// saved layout: q f32 [A] | Ut [H, d] | a32 [T, H, V] ([T, V, H] on the streaming path) | xbar [T, H, d]
-//               | zh [T, A] | zh - b_v [T, A] (streaming path)
+// saved layout: q f32 [A] | Ut [H, d] | a32 [T, H, V] ([T, V, H] on the streaming path) | xbar [T, H, d] | zh [T, A]
 struct Saved {
-  float* q; void* Ut; float* a32; void* xbar; void* zh; void* vh;
+  float* q; void* Ut; float* a32; void* xbar; void* zh;
 };
 Saved carve_saved(const Sizes& z, orbit_dtype dt, void* base, size_t* used) {
   Carver c(base);
@@ -643,7 +642,6 @@ Saved carve_saved(const Sizes& z, orbit_dtype dt, void* base, size_t* used) {
   s.a32 = c.take<float>((size_t)z.T * z.H * z.V);
   s.xbar = c.take<char>((size_t)z.T * z.H * z.d * esz(dt));
   s.zh = c.take<char>((size_t)z.T * z.A * esz(dt));
-  s.vh = agg_stream_ok(dt, z.V, z.d, z.H) ? c.take<char>((size_t)z.T * z.A * esz(dt)) : nullptr;
   if (used) *used = c.used();
   return s;
 }
@@ -692,8 +690,8 @@ size_t agg_saved_bytes(const orbit_agg_desc& a) {
 }
 
 // forward workspace: S f32 [T*V, H] | ab [T, H, Vp] | query partials | gemm split-K
-// backward workspace: dzh [T, A] | dxbar [T, H, d] | da f32 [T, H, V] | ac [T*V, 2H] (streaming path: row sums f32
-//                     [T, 16] | dU partials) | dU f32 [d, H] | dq f32 [A] | query-gradient partials | colsum
+// backward workspace: dzh [T, A] | dxbar [T, H, d] | da f32 [T, H, V] | ac [T*V, 2H] (streaming path: dU
+//                     partials) | dU f32 [d, H] | dq f32 [A] | query-gradient partials | colsum
 //                     | gemm split-K
 static size_t gemm_ws_max(const Sizes& z, orbit_dtype dt) {
   // split-K partials of every product of the forward and backward passes
@@ -726,7 +724,6 @@ size_t agg_workspace_bytes(const orbit_agg_desc& a) {
   b.take<char>((size_t)z.T * z.A * esz(dt));
   b.take<char>((size_t)z.T * z.H * z.d * esz(dt));
   if (stream) {
-    b.take<float>((size_t)z.T * 16);
     b.take<float>((size_t)agg_stream_blocks(z.T, z.d) * z.H * agg_stream_cols(z.d));
   } else {
     b.take<float>((size_t)z.T * z.H * z.V);
@@ -822,9 +819,6 @@ orbit_status agg_forward(const orbit_agg_desc& a, const void* tok, const orbit_a
     g.B = p.w_v; g.ldb = z.A; g.b_kmajor = false; g.sB = z.dh;
     g.C = sv.zh; g.ldc = z.A; g.sC = z.dh;
     g.bias = p.b_v; g.sBias = z.dh;
-    // the streaming backward's row sums come from the outputs before the bias:
-    // a bias larger than they are would leave few of their bits in zh
-    g.raw_out = sv.vh; g.ldraw = z.A; g.sRaw = z.dh;
     g.M = (int)z.T; g.N = z.dh; g.K = z.d; g.batch = z.H;
     ORBIT_TRY(gemm(g, gws, gws_bytes, s));
   }
@@ -853,10 +847,9 @@ orbit_status agg_backward(const orbit_agg_desc& a, const void* tok, const orbit_
   void* dzh = w.take<char>((size_t)z.T * z.A * esz(dt));
   void* dxbar = w.take<char>((size_t)z.T * z.H * z.d * esz(dt));
   const bool stream = agg_stream_ok(dt, z.V, z.d, z.H);
-  float *da = nullptr, *rowsum = nullptr, *du_part = nullptr;
+  float *da = nullptr, *du_part = nullptr;
   void* ac = nullptr;
   if (stream) {
-    rowsum = w.take<float>((size_t)z.T * 16);
     du_part = w.take<float>((size_t)agg_stream_blocks(z.T, z.d) * z.H * agg_stream_cols(z.d));
   } else {
     da = w.take<float>((size_t)z.T * z.H * z.V);
@@ -942,11 +935,9 @@ orbit_status agg_backward(const orbit_agg_desc& a, const void* tok, const orbit_
     ORBIT_TRY(gemm(g, gws, gws_bytes, s));
   }
   if (stream) {
-    ORBIT_TRY(agg_stream_rowsum(static_cast<const bf16*>(sv.vh), static_cast<const bf16*>(dzh), rowsum, z.T, z.H, z.dh,
-                                s));
     ORBIT_TRY(agg_stream_bwd(static_cast<const bf16*>(tok), static_cast<const bf16*>(dxbar),
-                             static_cast<const bf16*>(sv.Ut), sv.a32, rowsum, static_cast<const bf16*>(sv.xbar),
-                             static_cast<bf16*>(dtok), du_part, dU, z.T, z.V, z.d, z.H, scale, s));
+                             static_cast<const bf16*>(sv.Ut), sv.a32, static_cast<bf16*>(dtok), du_part, dU, z.T, z.V,
+                             z.d, z.H, scale, s));
   } else {
     // da_t [H, V] = dxbar_t [H, d] X_t^T
     if (rowdot_ok(dt, z, tok, dxbar)) {

@@ -1,5 +1,5 @@
-// Single-pass streaming kernels of the variable aggregation (bf16, 8 or 16
-// heads, embeddings up to 2048): each direction reads the token tensor once.
+// Streaming kernels of the variable aggregation (bf16, 8 or 16 heads, embeddings
+// up to 2048): each direction takes the token tensor from HBM once.
 #pragma once
 #include "common.h"
 
@@ -19,14 +19,9 @@ int agg_stream_cols(int d);
 orbit_status agg_stream_fwd(const bf16* tok, const bf16* Ut, float* a32, bf16* xbar, int64_t T, int V, int d, int H,
                             float scale, hipStream_t s);
 
-// cp[t][16]: the softmax backward's row sums c_h = sum_v a_v (x_v . dxbar_h)
-// from the stored value outputs before their bias, vh_h . dzh_h
-orbit_status agg_stream_rowsum(const bf16* vh, const bf16* dzh, float* cp, int64_t T, int H, int dh, hipStream_t s);
-
-// dA, softmax backward, dtok and the partials of dU in one pass; dU [d, H]
+// dA, softmax backward, dtok and the partials of dU in one kernel; dU [d, H]
 // float32 is finished from the partials
-orbit_status agg_stream_bwd(const bf16* tok, const bf16* dxbar, const bf16* Ut, const float* a32, const float* cp,
-                            const bf16* xbar, bf16* dtok, float* part, float* dU, int64_t T, int V, int d, int H,
-                            float scale, hipStream_t s);
+orbit_status agg_stream_bwd(const bf16* tok, const bf16* dxbar, const bf16* Ut, const float* a32, bf16* dtok,
+                            float* part, float* dU, int64_t T, int V, int d, int H, float scale, hipStream_t s);
 
 }  // namespace orbit

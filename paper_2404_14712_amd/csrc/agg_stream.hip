@@ -1,30 +1,36 @@
-// Variable aggregation in one pass over the token tensor per direction (bf16).
+// Variable aggregation with the patch-coupling steps inside one kernel per
+// direction (bf16).
 //
 // What bounds these kernels is HBM: the token tensor is the largest of the
 // path, and the general path reads it twice forward (scores, xbar) and twice
 // backward (dA, dU) besides writing its gradient. Here a block owns whole
 // patches and keeps what couples the passes (running softmax, xbar and dU
 // accumulators, the folded keys and dxbar as MFMA fragments) in registers, so
-// a row of tokens is read once per direction:
+// a row of tokens comes from HBM once per direction:
 //
 //   forward:  S = X U^T, online softmax over the variables, xbar += P^T X
-//   backward: dA = X dxbar^T, dS = a (dA - c) scale, dtok = [a | dS][dxbar; U],
-//             dU += dS^T X
+//   backward: dA = X dxbar^T, c = sum_v a_v dA_v,
+//             then dS = a (dA - c) scale, dtok = [a | dS][dxbar; U], dU += dS^T X
 //
-// c_h = sum_v a_v dA_v couples the rows of a patch. It equals xbar_h . dxbar_h
-// = vh_h . dzh_h (vh: the value outputs before their bias, stored by the
-// forward; zh - b_v would lose their bits to a large bias), which is known
-// before the pass, up to the bf16 rounding of vh and dxbar. The pass sums the
-// exact c alongside, and what the rounding did to dU, (c' - c) scale xbar_h, is
-// added at the patch's end.
+// c couples the rows of a patch, so the backward sweeps a patch twice: its
+// second reads (in reverse, the last slot still being in LDS) come from the
+// caches. c has to be the sum of the very dA it is subtracted from: what the
+// variables of a patch have in common is the same large number in every dA_v
+// and in c, and the softmax does not see it. A c known before the sweep (the
+// value outputs' product v_h . dzh_h, whose rounding is not that of dxbar) costs
+// 15 us less on the first shape below but leaves 2^-9 of the common part in
+// dtok: with a common part of 16 times the tokens' spread its largest error was
+// 2e-2 to 7e-2 of the largest element, with 256 times up to 1.1 (now 8e-3).
 //
 // Eight waves share a block; wave w owns columns [w CPW, (w + 1) CPW) of every
 // row. Rows arrive in slots of 16 variables x DP = 8 CPW columns, copied by the
-// buffer unit straight into an NS-deep LDS ring (64 to 144 KB), non-temporally
-// (plain: backward 356 against 332 us below). A slot is read twice from LDS: as
-// row fragments (scores, dA: the reduction runs over the columns, wave sums are
-// added in order through LDS) and through transposing reads (xbar, dU: the
-// reduction runs over the variables). The 16-byte chunk index of a row is
+// buffer unit straight into an NS-deep LDS ring (64 to 144 KB). A slot is read
+// from LDS as row fragments (scores, dA: the reduction runs over the columns,
+// wave sums are added in order through LDS) and through transposing reads
+// (xbar, dU: the reduction runs over the variables). Copies are non-temporal
+// but for the rows that the backward reads again (all of them non-temporal:
+// 720 against 626 us for the first shape's whole backward; all of them plain:
+// 1-5% slower on five of six large shapes). The 16-byte chunk index of a row is
 // XORed with f(r) = 4 (r mod 4) + (r / 4) mod 4, a permutation of 0..15 whose
 // four consecutive rows land 64 bytes apart, so both reads are free of bank
 // conflicts. Slots of 8 rows (twice as many in flight) were slower everywhere
@@ -32,11 +38,12 @@
 // fixed cost per slot, then bounds it); at DP = 512 two blocks per CU with four
 // slots each hide that cost (forward 114 -> 100 us against one with eight).
 //
-// Measured on MI355X, kernels of the general path -> this pass:
+// Measured on MI355X, kernels of the general path -> these:
 //   8192 patches x 48 variables x 1024, 16 heads: forward (scores + softmax +
-//   xbar) 427 -> 210 us (5.2 TB/s), backward (dA + softmax + dU + dtok)
-//   680 -> 333 us (5.7 TB/s);
-//   1770 x 67 x 2048, 16 heads: 248 -> 130 us (4.7), 402 -> 229 us (5.3).
+//   xbar) 427 -> 198 us (5.6 TB/s), backward (dA + softmax + dU + dtok)
+//   680 -> 357 us (5.3 TB/s);
+//   1770 x 67 x 2048, 16 heads: 248 -> 124 us (4.9), 402 -> 254 us (4.3 TB/s:
+//   two slots of 64 KB leave little in flight).
 #include <algorithm>
 
 #include "agg_stream.h"
@@ -105,10 +112,14 @@ struct SlotCopy {
     }
   }
   // rows row0.. of the matrix at `base` (`bytes` long; rows past it read zeros)
+  template <bool NT>
   ORBIT_DEV void issue(const void* base, int bytes, unsigned row_off, unsigned lds, int wave) const {
     const __amdgpu_buffer_rsrc_t rs = rsrc(base, bytes);
 #pragma unroll
-    for (int j = 0; j < C::NLD; ++j) dma16nt(rs, lds + (wave * C::NLD + j) * 1024, voff[j] + row_off);
+    for (int j = 0; j < C::NLD; ++j) {
+      if constexpr (NT) dma16nt(rs, lds + (wave * C::NLD + j) * 1024, voff[j] + row_off);
+      else dma16(rs, lds + (wave * C::NLD + j) * 1024, voff[j] + row_off);
+    }
   }
 };
 
@@ -196,8 +207,8 @@ __global__ void __launch_bounds__(kThreads, 2 * C::BPC) agg_stream_fwd_kernel(co
   int it_t = blockIdx.x, it_c = 0, it_n = 0;
   auto issue = [&]() {
     const bool live = it_n < total;
-    cp.issue(tok + (live ? (int64_t)it_t * V * d : 0), live ? V * d * 2 : 0, (unsigned)(it_c * R * d) * 2u,
-             lds0 + (it_n % NS) * C::SLOT, wave);
+    cp.template issue<true>(tok + (live ? (int64_t)it_t * V * d : 0), live ? V * d * 2 : 0, (unsigned)(it_c * R * d) * 2u,
+                            lds0 + (it_n % NS) * C::SLOT, wave);
     ++it_n;
     if (++it_c == nch) { it_c = 0; it_t += gridDim.x; }
   };
@@ -304,48 +315,22 @@ __global__ void __launch_bounds__(kThreads, 2 * C::BPC) agg_stream_fwd_kernel(co
 // ---------------------------------------------------------------------------
 // backward
 // ---------------------------------------------------------------------------
-// vh_h . dzh_h per (token, head): 8 lanes each
-__global__ void __launch_bounds__(256) agg_stream_rowsum_kernel(const bf16* __restrict__ vh,
-                                                                const bf16* __restrict__ dzh, float* __restrict__ cp,
-                                                                int64_t n, int H, int dh) {
-  const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 3;
-  const int sub = threadIdx.x & 7;
-  if (i >= n) return;
-  const int64_t t = i / H;
-  const int h = (int)(i - t * H);
-  const int64_t off = t * H * dh + (int64_t)h * dh;
-  float s = 0.f;
-  for (int j = sub * 8; j < dh; j += 64) {
-    float z[8], g[8];
-    unpack(ld128(vh + off + j), z, (bf16*)nullptr);
-    unpack(ld128(dzh + off + j), g, (bf16*)nullptr);
-#pragma unroll
-    for (int u = 0; u < 8; ++u) s += z[u] * g[u];
-  }
-#pragma unroll
-  for (int o = 1; o < 8; o <<= 1) s += __shfl_xor(s, o, 64);
-  if (sub == 0) cp[t * 16 + h] = s;
-}
-
-// RECOMP: the patch's xbar is accumulated again beside dU; otherwise it is
-// read back as the patch's last slot (CPW 256: it would spill)
-template <typename C, bool RECOMP>
+template <typename C>
 __global__ void __launch_bounds__(kThreads, 2 * C::BPC) agg_stream_bwd_kernel(
     const bf16* __restrict__ tok, const bf16* __restrict__ dxbar, const bf16* __restrict__ Ut,
-    const float* __restrict__ a32, const float* __restrict__ cpv, const bf16* __restrict__ xbar,
-    bf16* __restrict__ dtok, float* __restrict__ dupart, int T, int V, int d, int H, float scale) {
+    const float* __restrict__ a32, bf16* __restrict__ dtok, float* __restrict__ dupart, int T, int V, int d, int H,
+    float scale) {
   constexpr int NS = C::NS, KS = C::KS;
-  constexpr int AP = 40, SP = 20;          // pitches (bf16) of the [a | dS] rows and of dS^T
+  constexpr int SP = 20;                   // pitch (bf16) of dS^T
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, q = lane & 15;
-  char* aring = smem + NS * C::SLOT;       // per slot 1 KB: the rows' weights, or c'
+  char* aring = smem + NS * C::SLOT;       // per slot 1 KB: the rows' weights
   char* part = aring + NS * 1024;          // 8 KB wave partials of dA
-  bf16* ads = reinterpret_cast<bf16*>(part + 8192);  // [16 variables][a (16 heads) | dS (16 heads)]
-  bf16* dst = ads + 16 * AP;                         // dS^T [16 heads][16 variables]
-  bf16* att = dst + 16 * SP;                         // a^T (RECOMP)
-  float* red = reinterpret_cast<float*>(att + 16 * SP);  // [4][16] partials of c
+  bf16* ads = reinterpret_cast<bf16*>(part + 8192);   // [2][16 variables][a (16 heads) | dS (16 heads)], swizzled
+  bf16* dst = ads + 2 * 16 * 32;                      // dS^T [2][16 heads][16 variables]
+  float* red = reinterpret_cast<float*>(dst + 2 * 16 * SP);  // [8][16] chunk sums of a dA
   const unsigned lds0 = (unsigned)(uintptr_t)(ORBIT_LDS void*)smem;
   const unsigned lds_a = lds0 + NS * C::SLOT;
 
@@ -355,12 +340,14 @@ __global__ void __launch_bounds__(kThreads, 2 * C::BPC) agg_stream_bwd_kernel(
   fr.init(wave, lane);
 
   const int nch = (V + R - 1) / R;
-  // a patch's slots: dxbar, the token rows (nch), xbar (unless RECOMP); the
+  // a patch's slots: dxbar, its chunks of 16 rows (dA), then all but the last
+  // of them again in reverse (dS, dtok, dU: the last one is still there); the
   // block's first slot holds U
-  const int per = 1 + nch + (RECOMP ? 0 : 1);
+  const int per = 2 * nch;
   const int npatch = (T - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;
   const int total = 1 + npatch * per;
-  int it_t = (int)blockIdx.x - (int)gridDim.x, it_k = per - 1, it_n = 0;  // U counts as the tail of a patch before the first
+  int it_t = (int)blockIdx.x - (int)gridDim.x, it_k = per - 1;  // U counts as the tail of a patch before the first
+  int it_n = 0, it_s = 0;  // slots copied so far, ring position of the next
   auto issue = [&]() {
     const bool live = it_n < total;
     const void* base = tok;
@@ -373,18 +360,20 @@ __global__ void __launch_bounds__(kThreads, 2 * C::BPC) agg_stream_bwd_kernel(
         base = Ut; bytes = H * d * 2;
       } else if (it_k == 0) {
         base = dxbar + (int64_t)it_t * H * d; bytes = H * d * 2;
-        abase = cpv + (int64_t)it_t * 16; abytes = 64;
-      } else if (it_k <= nch) {
-        base = tok + (int64_t)it_t * V * d; bytes = V * d * 2; row0 = (it_k - 1) * R;
-        abase = a32 + (int64_t)it_t * V * H; abytes = V * H * 4; aoff = (unsigned)(row0 * H) * 4u;
       } else {
-        base = xbar + (int64_t)it_t * H * d; bytes = H * d * 2;
+        base = tok + (int64_t)it_t * V * d; bytes = V * d * 2;
+        row0 = (it_k <= nch ? it_k - 1 : 2 * nch - 1 - it_k) * R;
+        if (it_k <= nch) {
+          abase = a32 + (int64_t)it_t * V * H; abytes = V * H * 4; aoff = (unsigned)(row0 * H) * 4u;
+        }
       }
     }
-    const int sl = it_n % NS;
-    cp.issue(base, bytes, (unsigned)(row0 * d) * 2u, lds0 + sl * C::SLOT, wave);
-    if (wave == 7) dma16(rsrc(abase, abytes), lds_a + sl * 1024, lane * 16 < R * H * 4 ? (unsigned)lane * 16u + aoff : kOob);
+    // rows that come back for the second sweep stay in the caches
+    if (it_k == 0 || it_k >= nch) cp.template issue<true>(base, bytes, (unsigned)(row0 * d) * 2u, lds0 + it_s * C::SLOT, wave);
+    else cp.template issue<false>(base, bytes, (unsigned)(row0 * d) * 2u, lds0 + it_s * C::SLOT, wave);
+    if (wave == 7) dma16(rsrc(abase, abytes), lds_a + it_s * 1024, lane * 16 < R * H * 4 ? (unsigned)lane * 16u + aoff : kOob);
     ++it_n;
+    if (++it_s == NS) it_s = 0;
     if (++it_k == per) { it_k = 0; it_t += gridDim.x; }
   };
 #pragma unroll
@@ -393,7 +382,6 @@ __global__ void __launch_bounds__(kThreads, 2 * C::BPC) agg_stream_bwd_kernel(
   bf16x8 dxf[KS];            // dxbar: head q, columns 32 ks + 8 g
   bf16x8 duf[C::TILES];      // [dxbar; U]^T: column per lane, heads 8 g .. + 7 (U for g >= 2)
   f32x4 du[C::TILES];        // dU^T: columns 8 g.. of the pair, head q
-  f32x4 xb[RECOMP ? C::TILES : 1];
 #pragma unroll
   for (int i = 0; i < KS; ++i) dxf[i] = __builtin_bit_cast(bf16x8, zero128());
 #pragma unroll
@@ -401,9 +389,6 @@ __global__ void __launch_bounds__(kThreads, 2 * C::BPC) agg_stream_bwd_kernel(
     duf[i] = __builtin_bit_cast(bf16x8, zero128());
     du[i] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-#pragma unroll
-  for (int i = 0; i < (RECOMP ? C::TILES : 1); ++i) xb[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float cph = 0.f, csum = 0.f;
 
   // transposed 8-head fragments of a [16, DP] slot for the lanes with `take`
   // (once per patch: the addresses are formed here each time instead of being
@@ -433,8 +418,8 @@ __global__ void __launch_bounds__(kThreads, 2 * C::BPC) agg_stream_bwd_kernel(
     }
   };
 
-  unsigned hist = 0;  // token slots (which store) among the last NS - 1 slots
-  int it = 0;         // slots used so far
+  unsigned hist = 0;  // slots after which dtok was stored among the last NS - 1
+  int used = NS - 1;  // ring position of the slot in use
   // wait for the next slot, hand the one before it to the copies
   auto next_slot = [&]() -> const char* {
     const int cnt = __builtin_popcount(hist);
@@ -443,27 +428,21 @@ __global__ void __launch_bounds__(kThreads, 2 * C::BPC) agg_stream_bwd_kernel(
     lds_barrier();
     issue();
     hist = (hist << 1) & ((1u << (NS - 1)) - 1);
-    return smem + (it++ % NS) * C::SLOT;
+    if (++used == NS) used = 0;
+    return smem + used * C::SLOT;
   };
-  auto aslot = [&]() -> const char* { return aring + ((it - 1) % NS) * 1024; };
 
   take_tr(next_slot(), g >= 2);
   for (int t = blockIdx.x; t < T; t += gridDim.x) {
-    {
-      const char* slot = next_slot();
-      take_tr(slot, g < 2);
+    const char* slot = next_slot();
+    take_tr(slot, g < 2);
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) dxf[ks] = fr.read_row(slot, ks);
-      // heads past H (H = 8) have no row sum: their weights are zero, and a
-      // stray value must not meet them
-      cph = q < H ? *reinterpret_cast<const float*>(aslot() + q * 4) : 0.f;
-    }
-    csum = 0.f;
-    const __amdgpu_buffer_rsrc_t rd = rsrc(dtok + (int64_t)t * V * d, V * d * 2);
+    for (int ks = 0; ks < KS; ++ks) dxf[ks] = fr.read_row(slot, ks);
+    // first sweep: dA of every chunk; wave w keeps chunk w (variables 16 w + 4 g
+    // .. + 3, head q), with the weights
+    f32x4 da = f32x4{0.f, 0.f, 0.f, 0.f}, wa = da;
     for (int c = 0; c < nch; ++c) {
-      const char* slot = next_slot();
-      const char* as = aslot();
-      const bool last = c == nch - 1;
+      slot = next_slot();
       // dA [variable, head] of this wave's columns
       f32x4 s4 = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -473,53 +452,57 @@ __global__ void __launch_bounds__(kThreads, 2 * C::BPC) agg_stream_bwd_kernel(
       }
       *reinterpret_cast<f32x4*>(part + wave * 1024 + lane * 16) = s4;
       lds_barrier();
-      // one (variable, head) pair per thread of the first four waves: variable
-      // 4 wave + g, head q
-      const int v = 4 * wave + g;
-      float a = 0.f, da = 0.f;
-      if (wave < 4) {
-        const float* pp = reinterpret_cast<const float*>(part + wave * 256 + q * 16 + g * 4);
-        da = pp[0];
+      if (c == wave) {
+        da = *reinterpret_cast<const f32x4*>(part + lane * 16);
 #pragma unroll
-        for (int w = 1; w < 8; ++w) da += pp[w * 256];
-        const bool ok = c * R + v < V && q < H;
-        a = ok ? *reinterpret_cast<const float*>(as + (v * H + q) * 4) : 0.f;
-        da = ok ? da : 0.f;
-        csum += a * da;
-        if (last) {
-          float x = csum;
-          x += __shfl_xor(x, 16, 64);
-          x += __shfl_xor(x, 32, 64);
-          if (g == 0) red[wave * 16 + q] = x;
+        for (int w = 1; w < 8; ++w) da += *reinterpret_cast<const f32x4*>(part + w * 1024 + lane * 16);
+        const float* as = reinterpret_cast<const float*>(aring + used * 1024);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const bool ok = c * R + 4 * g + r < V && q < H;
+          wa[r] = ok ? as[(4 * g + r) * H + q] : 0.f;
+          da[r] = ok ? da[r] : 0.f;
         }
       }
-      if (nch == 1) {
-        // the whole patch is here: its exact c (with one variable dS vanishes)
-        lds_barrier();
-        cph = (red[q] + red[16 + q]) + (red[32 + q] + red[48 + q]);
+    }
+    // c = sum_v a_v dA_v, then dS of this wave's chunk (zero past the variables and heads)
+    float x = (wa[0] * da[0] + wa[1] * da[1]) + (wa[2] * da[2] + wa[3] * da[3]);
+    x += __shfl_xor(x, 16, 64);
+    x += __shfl_xor(x, 32, 64);
+    if (g == 0) red[wave * 16 + q] = x;
+    lds_barrier();
+    float cs = red[q];
+#pragma unroll
+    for (int w = 1; w < 8; ++w) cs += red[w * 16 + q];
+    auto put = [&](int c, int buf) {
+      s16x4 dt;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int v = 4 * g + r;
+        const bool ok = c * R + v < V && q < H;
+        const bf16 ds = (bf16)(ok ? wa[r] * (da[r] - cs) * scale : 0.f);
+        bf16* row = ads + (buf * 16 + v) * 32 + (q & 7);
+        row[((q >> 3) ^ g) * 8] = (bf16)wa[r];
+        row[((2 + (q >> 3)) ^ g) * 8] = ds;
+        dt[r] = __builtin_bit_cast(short, ds);
       }
-      if (wave < 4) {
-        const float ds = a * (da - cph) * scale;
-        ads[v * AP + q] = (bf16)a;
-        ads[v * AP + 16 + q] = (bf16)ds;
-        dst[q * SP + v] = (bf16)ds;
-        if (RECOMP) att[q * SP + v] = (bf16)a;
-      }
-      lds_barrier();
-      const bf16x8 adf = *reinterpret_cast<const bf16x8*>(ads + q * AP + g * 8);
-      const s16x4 dsf = *reinterpret_cast<const s16x4*>(dst + q * SP + g * 4);
-      s16x4 atf = dsf;
-      if (RECOMP) atf = *reinterpret_cast<const s16x4*>(att + q * SP + g * 4);
+      *reinterpret_cast<s16x4*>(dst + (buf * 16 + q) * SP + 4 * g) = dt;
+    };
+    if (wave == nch - 1) put(wave, 0);
+    lds_barrier();
+    // second sweep, last chunk first
+    const __amdgpu_buffer_rsrc_t rd = rsrc(dtok + (int64_t)t * V * d, V * d * 2);
+    for (int c = nch - 1, buf = 0; c >= 0; --c, buf ^= 1) {
+      if (c != nch - 1) slot = next_slot();
+      if (wave == c - 1) put(wave, buf ^ 1);
+      const bf16x8 adf = *reinterpret_cast<const bf16x8*>(ads + (buf * 16 + q) * 32 + (g ^ (q >> 2)) * 8);
+      const s16x4 dsf = *reinterpret_cast<const s16x4*>(dst + (buf * 16 + q) * SP + g * 4);
       const unsigned vo = (unsigned)((c * R + q) * d + wave * C::CPW + g * 8) * 2u;
 #pragma unroll
       for (int p = 0; p < KS; ++p) {
         const s16x4 x0 = fr.read_tr(slot, p, 0), x1 = fr.read_tr(slot, p, 1);
         du[2 * p] = mma16x(x0, dsf, du[2 * p]);
         du[2 * p + 1] = mma16x(x1, dsf, du[2 * p + 1]);
-        if (RECOMP) {
-          xb[2 * p] = mma16x(x0, atf, xb[2 * p]);
-          xb[2 * p + 1] = mma16x(x1, atf, xb[2 * p + 1]);
-        }
         const f32x4 z4 = f32x4{0.f, 0.f, 0.f, 0.f};
         const f32x4 o0 = mma32(duf[2 * p], adf, z4), o1 = mma32(duf[2 * p + 1], adf, z4);
         const u32x4 o = {pack2(o0[0], o0[1]), pack2(o0[2], o0[3]), pack2(o1[0], o1[1]), pack2(o1[2], o1[3])};
@@ -529,28 +512,6 @@ __global__ void __launch_bounds__(kThreads, 2 * C::BPC) agg_stream_bwd_kernel(
         if (p & 1) __builtin_amdgcn_sched_barrier(0);
       }
       hist |= 1u;
-    }
-    // what the rounding of c' did to dU
-    const float cx = (red[q] + red[16 + q]) + (red[32 + q] + red[48 + q]);
-    const float delta = (cph - cx) * scale;
-    if constexpr (RECOMP) {
-#pragma unroll
-      for (int i = 0; i < C::TILES; ++i) {
-        du[i] += delta * xb[i];
-        xb[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-      }
-    } else {
-      const char* slot = next_slot();
-#pragma unroll
-      for (int p = 0; p < KS; ++p) {
-        const bf16x8 x = fr.read_row(slot, p);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          du[2 * p][r] += delta * (float)x[r];
-          du[2 * p + 1][r] += delta * (float)x[4 + r];
-        }
-        if (p & 1) __builtin_amdgcn_sched_barrier(0);
-      }
     }
   }
   wait_vmcnt<0>();
@@ -614,18 +575,17 @@ orbit_status run_fwd(const bf16* tok, const bf16* Ut, float* a32, bf16* xbar, in
                 xbar, (int)T, V, d, H, scale * 1.4426950408889634f);
 }
 
-template <typename C, bool RECOMP>
-orbit_status run_bwd(const bf16* tok, const bf16* dxbar, const bf16* Ut, const float* a32, const float* cp,
-                     const bf16* xbar, bf16* dtok, float* part, int64_t T, int V, int d, int H, float scale,
-                     hipStream_t s) {
-  constexpr size_t lds = C::NS * (C::SLOT + 1024) + 8192 + 16 * 40 * 2 + 2 * 16 * 20 * 2 + 256;
-  static_assert(lds <= 160 * 1024, "LDS");
-  static const bool once = (lift_lds(agg_stream_bwd_kernel<C, RECOMP>, lds), true);
+template <typename C>
+orbit_status run_bwd(const bf16* tok, const bf16* dxbar, const bf16* Ut, const float* a32, bf16* dtok, float* part,
+                     int64_t T, int V, int d, int H, float scale, hipStream_t s) {
+  constexpr size_t lds = C::NS * (C::SLOT + 1024) + 8192 + 2 * 16 * 32 * 2 + 2 * 16 * 20 * 2 + 8 * 16 * 4;
+  static_assert(lds * C::BPC <= 160 * 1024, "LDS");
+  static const bool once = (lift_lds(agg_stream_bwd_kernel<C>, lds), true);
   (void)once;
   KernelInfo k{"agg_stream_bwd", 8.0 * T * V * (double)H * d,
-               (double)T * (2 * V + (RECOMP ? 1 : 2) * H) * d * 2.0 + 4.0 * T * V * H};
-  return launch(k, agg_stream_bwd_kernel<C, RECOMP>, dim3((unsigned)blocks<C>(T)), dim3(kThreads), lds, s, tok,
-                dxbar, Ut, a32, cp, xbar, dtok, part, (int)T, V, d, H, scale);
+               (double)T * (2 * V + H) * d * 2.0 + 4.0 * T * V * H};
+  return launch(k, agg_stream_bwd_kernel<C>, dim3((unsigned)blocks<C>(T)), dim3(kThreads), lds, s, tok, dxbar, Ut, a32,
+                dtok, part, (int)T, V, d, H, scale);
 }
 
 }  // namespace
@@ -651,20 +611,14 @@ orbit_status agg_stream_fwd(const bf16* tok, const bf16* Ut, float* a32, bf16* x
   }
 }
 
-orbit_status agg_stream_rowsum(const bf16* vh, const bf16* dzh, float* cp, int64_t T, int H, int dh, hipStream_t s) {
-  KernelInfo k{"agg_stream_rowsum", 0.0, (double)T * H * dh * 4.0};
-  return launch(k, agg_stream_rowsum_kernel, dim3((unsigned)cdiv(T * H, 32)), dim3(256), 0, s, vh, dzh, cp, T * H, H, dh);
-}
-
-orbit_status agg_stream_bwd(const bf16* tok, const bf16* dxbar, const bf16* Ut, const float* a32, const float* cp,
-                            const bf16* xbar, bf16* dtok, float* part, float* dU, int64_t T, int V, int d, int H,
-                            float scale, hipStream_t s) {
+orbit_status agg_stream_bwd(const bf16* tok, const bf16* dxbar, const bf16* Ut, const float* a32, bf16* dtok,
+                            float* part, float* dU, int64_t T, int V, int d, int H, float scale, hipStream_t s) {
   orbit_status st;
   switch (cpw_of(d)) {
-    case 64: st = run_bwd<C64, true>(tok, dxbar, Ut, a32, cp, xbar, dtok, part, T, V, d, H, scale, s); break;
-    case 128: st = run_bwd<C128, true>(tok, dxbar, Ut, a32, cp, xbar, dtok, part, T, V, d, H, scale, s); break;
-    case 192: st = run_bwd<C192, true>(tok, dxbar, Ut, a32, cp, xbar, dtok, part, T, V, d, H, scale, s); break;
-    default: st = run_bwd<C256, false>(tok, dxbar, Ut, a32, cp, xbar, dtok, part, T, V, d, H, scale, s); break;
+    case 64: st = run_bwd<C64>(tok, dxbar, Ut, a32, dtok, part, T, V, d, H, scale, s); break;
+    case 128: st = run_bwd<C128>(tok, dxbar, Ut, a32, dtok, part, T, V, d, H, scale, s); break;
+    case 192: st = run_bwd<C192>(tok, dxbar, Ut, a32, dtok, part, T, V, d, H, scale, s); break;
+    default: st = run_bwd<C256>(tok, dxbar, Ut, a32, dtok, part, T, V, d, H, scale, s); break;
   }
   ORBIT_TRY(st);
   const int nb = agg_stream_blocks(T, d), DP = agg_stream_cols(d);

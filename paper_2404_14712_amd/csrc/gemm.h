@@ -20,7 +20,6 @@ struct Gemm {
   // epilogue, applied in this order to the float32 accumulator v:
   float alpha = 1.f;                             // v *= alpha
   bool accumulate = false;                       // v += C[m,n]     (float32 C only)
-  void* raw_out = nullptr;   int64_t ldraw = 0, sRaw = 0; // store v (dtype; batch stride sRaw)
   const void* bias = nullptr; int64_t sBias = 0; // v += bias[n]    (dtype; batch stride sBias)
   void* gelu_out = nullptr;  int64_t ldgo = 0;   // store v (dtype), then v = GELU(v)
   const void* gelu_in = nullptr; int64_t ldgi = 0; // v *= GELU'(gelu_in[m,n])

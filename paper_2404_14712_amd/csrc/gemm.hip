@@ -932,12 +932,11 @@ orbit_status gemm_run(const Gemm& g, const TileCfg& t, int splits, void* ws, siz
   {
     auto al = [](int64_t x) { return x % 8 == 0; };
     auto ap = [](const void* p) { return p == nullptr || (reinterpret_cast<uintptr_t>(p) & 15u) == 0; };
-    a.vec_ok = al(g.N) && al(g.ldc) && al(g.sC) && al(g.ldraw) && al(g.sRaw) && al(g.sBias) && al(g.ldgo) && al(g.ldgi) && al(g.ldr) &&
-               al(g.sR) && ap(g.C) && ap(g.raw_out) && ap(g.bias) && ap(g.gelu_out) && ap(g.gelu_in) && ap(g.res);
+    a.vec_ok = al(g.N) && al(g.ldc) && al(g.sC) && al(g.sBias) && al(g.ldgo) && al(g.ldgi) && al(g.ldr) &&
+               al(g.sR) && ap(g.C) && ap(g.bias) && ap(g.gelu_out) && ap(g.gelu_in) && ap(g.res);
   }
   a.epi.alpha = g.alpha;
   a.epi.accumulate = g.accumulate ? 1 : 0;
-  a.epi.raw_out = g.raw_out; a.epi.ldraw = g.ldraw; a.epi.sRaw = g.sRaw;
   a.epi.bias = g.bias;
   a.epi.sBias = g.sBias;
   a.epi.gelu_out = g.gelu_out; a.epi.ldgo = g.ldgo;

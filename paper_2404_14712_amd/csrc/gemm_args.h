@@ -7,7 +7,6 @@ namespace orbit {
 struct Epi {
   float alpha;
   int accumulate;
-  void* raw_out; int64_t ldraw, sRaw;
   const void* bias; int64_t sBias;
   void* gelu_out; int64_t ldgo;
   const void* gelu_in; int64_t ldgi;
@@ -32,7 +31,6 @@ ORBIT_DEV void epi_apply(const Epi& e, int64_t bz, int r, int c, float v, OutT* 
   v *= e.alpha;
   const int64_t off = (int64_t)r * ldc + c;
   if (e.accumulate) v += to_f(C[off]);
-  if (e.raw_out) static_cast<T*>(e.raw_out)[bz * e.sRaw + (int64_t)r * e.ldraw + c] = from_f<T>(v);
   if (e.bias) v += to_f(static_cast<const T*>(e.bias)[bz * e.sBias + c]);
   if (e.gelu_out) {
     static_cast<T*>(e.gelu_out)[(int64_t)r * e.ldgo + c] = from_f<T>(v);
@@ -69,7 +67,6 @@ ORBIT_DEV void epi_apply8(const Epi& e, int64_t bz, int r, int c0, float* v, Out
 #pragma unroll
     for (int i = 0; i < 8; ++i) v[i] += t[i];
   }
-  if (e.raw_out) st8(static_cast<T*>(e.raw_out) + bz * e.sRaw + (int64_t)r * e.ldraw + c0, v);
   if (e.bias) {
     if (b8) {
 #pragma unroll

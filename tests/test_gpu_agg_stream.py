@@ -1,4 +1,4 @@
-"""The single-pass aggregation kernels (bf16, 8 or 16 heads, embeddings up to
+"""The streaming aggregation kernels (bf16, 8 or 16 heads, embeddings up to
 2048) against the fp64 oracle at the sizes where they can go wrong: embeddings
 around each instantiation's width and not filling it, variables around the
 16-row slots and at the ends of the range, fewer patches than blocks and
@@ -61,18 +61,11 @@ def test_agg_stream(lib, case):
         check(f"d{k}", host(g[k]), rg[k], tol, floor_ref=rg["b_q"])
 
 
-@pytest.mark.parametrize("V", [2, 40])
-def test_agg_stream_large_value_bias(lib, V):
-    """A value bias far above the value outputs: the token gradient does not see
-    it (the weights sum to one), so the bound is the usual one."""
+def _token_gradient(lib, tok, prm, dz, H, dh):
+    """dtok of the library, of the oracle, and the oracle's weights."""
     import torch
     from paper_2404_14712_amd._lib import AggDesc
-    B, L, d, H, dh = 1, 24, 512, 8, 64
-    c = synth.small_config("115m", dtype="bf16", B=B, L=L, V=V, d=d, agg_heads=H, agg_head_dim=dh, sigma=0.1)
-    tok = synth.normal(c.seed, "tok", (B, L, V, d), dtype="bf16")
-    prm = synth.make_params(c.seed, "agg", synth.agg_param_shapes(d, H * dh, L), 0.1, "bf16")
-    prm["b_v"] = np.full_like(prm["b_v"], 4096.0) * np.sign(prm["b_v"])
-    dz = synth.normal(c.seed, "dz", (B, L, d), dtype="bf16")
+    B, L, V, d = tok.shape
     desc = AggDesc(B, L, V, d, H, dh, 1)
     pd = {k: dev(v, "bf16") for k, v in prm.items()}
     tokd, dzd = dev(tok, "bf16"), dev(dz, "bf16")
@@ -86,4 +79,49 @@ def test_agg_stream_large_value_bias(lib, V):
     torch.cuda.synchronize()
     _, cache = O.agg_fwd(tok, prm, H)
     rdtok, _ = O.agg_bwd(dz, cache, prm)
-    check("dtok", host(dtok).reshape(rdtok.shape), rdtok, TOL["bf16"])
+    return host(dtok).reshape(rdtok.shape), rdtok, cache["a"]
+
+
+def _case(B, L, V, d, H, dh, sigma):
+    c = synth.small_config("115m", dtype="bf16", B=B, L=L, V=V, d=d, agg_heads=H, agg_head_dim=dh, sigma=sigma)
+    tok = synth.normal(c.seed, "tok", (B, L, V, d), dtype="bf16")
+    prm = synth.make_params(c.seed, "agg", synth.agg_param_shapes(d, H * dh, L), sigma, "bf16")
+    dz = synth.normal(c.seed, "dz", (B, L, d), dtype="bf16")
+    return c, tok, prm, dz
+
+
+@pytest.mark.parametrize("V", [17, 40])
+def test_agg_stream_large_value_bias(lib, V):
+    """A value bias far above the value outputs: the token gradient does not see
+    it (the weights sum to one), so the bound is the usual one."""
+    H, dh = 8, 64
+    _, tok, prm, dz = _case(1, 24, V, 512, H, dh, 0.1)
+    prm["b_v"] = np.full_like(prm["b_v"], 4096.0) * np.sign(prm["b_v"])
+    got, ref, _ = _token_gradient(lib, tok, prm, dz, H, dh)
+    check("dtok", got, ref, TOL["bf16"])
+
+
+# V, d, heads, head_dim, sigma: every instantiation, several slots with a short last one; sigma such that
+# the scores spread by about one over the variables
+COMMON = [(17, 512, 8, 64, 0.14), (40, 512, 16, 32, 0.14), (91, 1024, 16, 64, 0.1), (48, 1536, 8, 64, 0.08),
+          (67, 2048, 16, 128, 0.07), (128, 2048, 8, 64, 0.07)]
+
+
+@pytest.mark.parametrize("channels", [0, 4])
+@pytest.mark.parametrize("s", [4, 16, 64, 256])
+@pytest.mark.parametrize("V,d,H,dh,sigma", COMMON)
+def test_agg_stream_common_component(lib, V, d, H, dh, sigma, s, channels):
+    """Variables that share a component s times their spread (in every channel,
+    or in a few large ones): the softmax does not see what it adds to all of a
+    patch's scores, and neither may the token gradient, whose dS = a (dA - c)
+    has it in dA and in c. A row sum c that is rounded apart from dA leaves
+    2^-9 of it there: more than the usual bound from s = 16 on (all channels)
+    or from s = 64 to 256 on (four)."""
+    c, tok, prm, dz = _case(1, 6, V, d, H, dh, sigma)
+    common = synth.normal(c.seed, "common", (1, 6, 1, d), dtype="bf16")
+    if channels:
+        common[..., channels:] = 0
+    tok = synth.bf16_round(np.asarray(tok + s * common, np.float32))
+    got, ref, a = _token_gradient(lib, tok, prm, dz, H, dh)
+    assert 1.5 / V < a.max(-1).mean() < 0.9  # neither uniform weights nor single ones
+    check("dtok", got, ref, TOL["bf16"])
