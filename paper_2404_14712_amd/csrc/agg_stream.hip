@@ -251,12 +251,13 @@ __global__ void __launch_bounds__(kThreads, 2 * C::BPC) agg_stream_fwd_kernel(co
     cm = fmaxf(cm, __shfl_xor(cm, 16, 64));
     cm = fmaxf(cm, __shfl_xor(cm, 32, 64));
     const float mn = fmaxf(m, cm);
-    const float al = __builtin_amdgcn_exp2f(m - mn);
+    const float mr = mn == -INFINITY ? 0.f : mn;  // only scores of -inf so far: they weigh nothing
+    const float al = __builtin_amdgcn_exp2f(m - mr);
     if (c == wave) sk = s4;
     float p[4], ps = 0.f, pbs = 0.f;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      p[r] = __builtin_amdgcn_exp2f(s4[r] - mn);
+      p[r] = __builtin_amdgcn_exp2f(s4[r] - mr);
       ps += p[r];
     }
     u32x2 pw;

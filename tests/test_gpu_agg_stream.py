@@ -125,3 +125,27 @@ def test_agg_stream_common_component(lib, V, d, H, dh, sigma, s, channels):
     got, ref, a = _token_gradient(lib, tok, prm, dz, H, dh)
     assert 1.5 / V < a.max(-1).mean() < 0.9  # neither uniform weights nor single ones
     check("dtok", got, ref, TOL["bf16"])
+
+
+@pytest.mark.parametrize("slot", [0, 1])
+def test_agg_stream_infinite_scores(lib, slot):
+    """Variables whose scores overflow to -inf weigh nothing, also when they
+    fill the first slot of 16, before any finite score is known."""
+    import torch
+    from paper_2404_14712_amd._lib import AggDesc
+    L, V, d, H, dh = 5, 40, 512, 8, 32
+    _, tok, prm, _ = _case(1, L, V, d, H, dh, 0.1)
+    # the query is all ones, so u_h[0] = 4 dh in every head
+    prm["w_q"], prm["b_q"] = np.zeros_like(prm["w_q"]), np.ones_like(prm["b_q"])
+    prm["w_k"][0] = 4.0
+    tok[..., 0] = 0
+    tok[:, :, 16 * slot:16 * slot + 16, 0] = synth.bf16_round(np.float32(-3e38))
+    desc = AggDesc(1, L, V, d, H, dh, 1)
+    z = torch.zeros(1, L, d, dtype=torch.bfloat16, device="cuda")
+    saved = torch.full((lib.orbit_var_aggregate_saved_bytes(desc),), 255, dtype=torch.uint8, device="cuda")
+    ws = torch.full((lib.orbit_var_aggregate_workspace_bytes(desc),), 255, dtype=torch.uint8, device="cuda")
+    lib.orbit_var_aggregate(desc, dev(tok, "bf16"), {k: dev(v, "bf16") for k, v in prm.items()}, z, saved, ws)
+    torch.cuda.synchronize()
+    ref, cache = O.agg_fwd(tok, prm, H)
+    assert cache["a"][..., 16 * slot:16 * slot + 16].max() == 0
+    check("z", host(z), ref, TOL["bf16"])
