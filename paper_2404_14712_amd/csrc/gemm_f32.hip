@@ -3,17 +3,22 @@
 // The matrix cores run float32 operands at 1/16 of their bf16 rate (157 against
 // 2500 TFLOP/s nominal), so a float32 MFMA loop is bound by them. Here every
 // operand element is split on its way into LDS into three bf16 parts,
-// x = h + m + l (h: the upper 16 bits, m and l: the remainders rounded to
-// nearest), which together hold the 24 bits of x, and a product is the sum of
-// the six terms h h', h m', m h', m m', h l', l h' (the dropped ones are below
-// 2^-25 of it), accumulated in float32: 6/16 of the float32 MFMA time. The
+// x = h + m + l (each the remainder so far rounded to nearest), which together
+// hold the 24 bits of x, and a product is the sum of the six terms h h', h m',
+// m h', m m', h l', l h', accumulated in float32: 6/16 of the float32 MFMA
+// time. With |m| <= 2^-8 |x| and |l| <= 2^-17 |x| the dropped terms m l' + l m'
+// are at most 2^-24 of the product, half a float32 step (2^-27.5 in the root mean
+// square; h cut off instead of rounded: 2^-22 and 2^-25.5). The
 // leading term has an accumulator of its own, so the large sum is rounded once
 // per 16 k (float32 MFMA: every 2 k); against float64 the results are closer
-// than the float32 MFMA's (relative error over N(0,1) operands, K = 1024:
-// 1.9e-7 against 4.1e-7 unsplit; K = 4096: 3.9e-7 against 1.1e-6).
+// than the float32 MFMA's (2048 x 1024 over N(0,1) operands, relative error:
+// K = 1024: 1.3e-7 against 2.9e-7; K = 4096: 1.9e-7 against 5.8e-7).
+// The split is the triple-bf16 one of Henry, Tang and Heinecke, "Leveraging the
+// bfloat16 artificial intelligence datatype for higher-precision computations"
+// (ARITH 2019).
 //
-// A product that is not finite (an infinity would meet parts that are zero or
-// of the other sign) is found from the tile's accumulators, and that tile is
+// A product that is not finite (an infinity, or a value that rounds up to one as
+// bf16, would meet parts that are zero or of the other sign) is found from the tile's accumulators, and that tile is
 // computed again with float32 MFMA.
 //
 // 4 waves per block, a 128x128 or 64x64 tile; 16-deep K slices in two LDS
@@ -53,9 +58,10 @@ ORBIT_DEV uint32_t pk_rn(float lo, float hi) {
 
 // two floats -> the packed bf16 pairs of their three parts
 ORBIT_DEV void split2(uint32_t x0, uint32_t x1, uint32_t& h, uint32_t& m, uint32_t& l) {
-  h = __builtin_amdgcn_perm(x1, x0, 0x07060302u);
-  float r0 = __uint_as_float(x0) - __uint_as_float(x0 & 0xffff0000u);
-  float r1 = __uint_as_float(x1) - __uint_as_float(x1 & 0xffff0000u);
+  float r0 = __uint_as_float(x0), r1 = __uint_as_float(x1);
+  h = pk_rn(r0, r1);
+  r0 -= __uint_as_float(h << 16);
+  r1 -= __uint_as_float(h & 0xffff0000u);
   m = pk_rn(r0, r1);
   r0 -= __uint_as_float(m << 16);
   r1 -= __uint_as_float(m & 0xffff0000u);

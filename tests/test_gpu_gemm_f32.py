@@ -65,3 +65,18 @@ def test_gemm_f32_not_finite(lib, M, N, K):
     a[~torch.isfinite(a)] = 0
     err = ((C.double() - ref).abs() / (a.abs() @ b.abs()))[ok].max().item()
     assert err <= K * 2.0 ** -24, err
+
+
+@pytest.mark.parametrize("ak,bk", [(1, 0), (1, 1), (0, 0)])
+@pytest.mark.parametrize("x", [1 + 511 / 65536, 1 + 2.0 ** -8 - 2.0 ** -17])
+def test_gemm_f32_split_bound(lib, x, ak, bk):
+    """Operands whose second and third parts are the largest there are, all of
+    one sign, and a single 16-deep step: each product keeps all but 2^-24 of
+    itself, and the two sums are rounded, once each, and added."""
+    import torch
+    M, N, K = 6016, 6016, 16
+    A = torch.full((M, K) if ak else (K, M), x, device="cuda")
+    B = torch.full((N, K) if bk else (K, N), x, device="cuda")
+    C = _run(lib, torch, A, B, M, N, K, ak, bk)
+    ref = K * x * x
+    assert float((C.double() - ref).abs().max()) <= 3 * 2.0 ** -24 * ref
