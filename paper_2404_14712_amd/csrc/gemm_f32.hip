@@ -17,18 +17,23 @@
 // bfloat16 artificial intelligence datatype for higher-precision computations"
 // (ARITH 2019).
 //
-// A product that is not finite (an infinity, or a value that rounds up to one as
-// bf16, would meet parts that are zero or of the other sign) is found from the tile's accumulators, and that tile is
-// computed again with float32 MFMA.
+// Operands are split at 2^16 times their value, so that the last part of the
+// smallest float32 numbers is no smaller than the smallest bf16 (unscaled, a
+// value below 2^-110 would lose up to 2^-134; the scaling costs 2-4%, finding
+// such values while they are split and computing their tile again cost 4-13%).
+//
+// A tile whose accumulators are not finite is computed again with float32 MFMA:
+// an infinity would meet parts that are zero or of the other sign, and values
+// from 2^112 or sums from 2^96 on overflow when scaled.
 //
 // 4 waves per block, a 128x128 or 64x64 tile; 16-deep K slices in two LDS
 // buffers (three planes of [row][16] bf16, 48-byte rows: fragment reads are
 // free of bank conflicts), one barrier per slice; a slice is split and written
 // while the one before it is multiplied, and two more are in flight from
 // memory. Two 128x128 blocks share a CU. The matrix cores then do 1.2 PFLOP/s
-// of bf16 work, as in the bf16 products: 170-200 TFLOP/s of float32 at 8192
+// of bf16 work, as in the bf16 products: 180-200 TFLOP/s of float32 at 8192
 // rows (float32 MFMA: 115-130), and with 1024 rows, N = 4096, K = 1024:
-// 62 / 55 / 55 us forward / input / weight gradient against 98 / 93 / 98.
+// 61 / 57 / 57 us forward / input / weight gradient against 88 / 85 / 91.
 #include <type_traits>
 
 #include "gemm_f32.h"
@@ -56,9 +61,12 @@ ORBIT_DEV uint32_t pk_rn(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, v);
 }
 
-// two floats -> the packed bf16 pairs of their three parts
+// the operands' scale and the products' way back
+constexpr float kUp = 65536.f, kDown = 1.f / (kUp * kUp);
+
+// two floats -> the packed bf16 pairs of the three parts of kUp x
 ORBIT_DEV void split2(uint32_t x0, uint32_t x1, uint32_t& h, uint32_t& m, uint32_t& l) {
-  float r0 = __uint_as_float(x0), r1 = __uint_as_float(x1);
+  float r0 = __uint_as_float(x0) * kUp, r1 = __uint_as_float(x1) * kUp;
   h = pk_rn(r0, r1);
   r0 -= __uint_as_float(h << 16);
   r1 -= __uint_as_float(h & 0xffff0000u);
@@ -308,7 +316,7 @@ __global__ void __launch_bounds__(256, 2) gemm_f32_kernel(GemmKArgs g) {
 #pragma unroll
   for (int i = 0; i < TW; ++i)
 #pragma unroll
-    for (int j = 0; j < TW; ++j) acc[i][j] += accs[i][j];
+    for (int j = 0; j < TW; ++j) acc[i][j] = (acc[i][j] + accs[i][j]) * kDown;
   float probe = 0.f;
 #pragma unroll
   for (int i = 0; i < TW; ++i)
@@ -317,7 +325,7 @@ __global__ void __launch_bounds__(256, 2) gemm_f32_kernel(GemmKArgs g) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) probe = fmaf(acc[i][j][v], 0.f, probe);
   if (__syncthreads_or(!(probe == 0.f))) {
-    // an infinity or a NaN in the tile: again with float32 MFMA
+    // an infinity or a NaN: again with float32 MFMA
     constexpr int FD = 32;
     using FA = GemmStage<float, BT, FD, 256, AK>;
     using FB = GemmStage<float, BT, FD, 256, BKM>;

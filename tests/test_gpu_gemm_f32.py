@@ -44,8 +44,13 @@ def test_gemm_f32(lib, M, N, K, ak, bk):
     assert worst <= K * 2.0 ** -24, worst
 
 
-@pytest.mark.parametrize("M,N,K", [(40, 48, 64), (1032, 1032, 1032)])
-def test_gemm_f32_not_finite(lib, M, N, K):
+# 32x32 tiles; 128x128 with K split, and unsplit; 64x64
+FALLBACK = [(40, 48, 64), (1032, 1032, 1032), (2056, 2056, 1032), (4104, 64, 2056)]
+
+
+@pytest.mark.parametrize("ak,bk", [(1, 0), (1, 1), (0, 0)])
+@pytest.mark.parametrize("M,N,K", FALLBACK)
+def test_gemm_f32_not_finite(lib, M, N, K, ak, bk):
     """Infinities and NaN reach exactly the outputs that float32 arithmetic gives
     them, with the same sign; everything else stays finite and right. Values at
     the top of the float32 range, which bf16 rounding would overflow, stay finite."""
@@ -55,7 +60,7 @@ def test_gemm_f32_not_finite(lib, M, N, K):
     A[3, 5], A[7, 9], A[9, 1], A[11, 2] = float("inf"), float("nan"), float("-inf"), 3.4e38
     B[2] = 1e-3
     a, b = A.double(), B.double()
-    C = _run(lib, torch, A, B, M, N, K, 1, 0)
+    C = _run(lib, torch, A if ak else A.t().contiguous(), B.t().contiguous() if bk else B, M, N, K, ak, bk)
     ref = a @ b
     ok = torch.isfinite(ref)
     assert torch.equal(ok, torch.isfinite(C))
@@ -65,6 +70,26 @@ def test_gemm_f32_not_finite(lib, M, N, K):
     a[~torch.isfinite(a)] = 0
     err = ((C.double() - ref).abs() / (a.abs() @ b.abs()))[ok].max().item()
     assert err <= K * 2.0 ** -24, err
+
+
+@pytest.mark.parametrize("ak,bk", [(1, 0), (1, 1), (0, 0)])
+@pytest.mark.parametrize("M,N,K", FALLBACK)
+@pytest.mark.parametrize("rows,sa,sb", [("one", -126, 0), ("all", -126, 0), ("one", 116, -20), ("all", 55, 50)])
+def test_gemm_f32_range(lib, M, N, K, ak, bk, rows, sa, sb):
+    """Operands near the bottom of the float32 range, whose parts unscaled would
+    fall below the smallest bf16, and operands or products near its top, which
+    overflow when scaled, keep their 24 bits: the results' errors stay those of
+    K roundings that add up like a random walk."""
+    import torch
+    A, B = _operands(torch, M, N, K, 1, 0)
+    i = 37 if rows == "one" else slice(None)
+    A[i] *= 2.0 ** sa
+    B *= 2.0 ** sb
+    C = _run(lib, torch, A if ak else A.t().contiguous(), B.t().contiguous() if bk else B, M, N, K, ak, bk)
+    ref = A.double() @ B.double()
+    for r in (i, 38):
+        err = ((C.double() - ref)[r].norm() / ref[r].norm()).item()
+        assert err <= K ** 0.5 * 2.0 ** -24, err
 
 
 @pytest.mark.parametrize("ak,bk", [(1, 0), (1, 1), (0, 0)])
