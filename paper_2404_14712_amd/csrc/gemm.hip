@@ -946,11 +946,16 @@ orbit_status gemm_run(const Gemm& g, const TileCfg& t, int splits, void* ws, siz
     return g.out_f32 ? run_typed<bf16, float>(g, a, t, s) : run_typed<bf16, bf16>(g, a, t, s);
   }
   // float operands always produce float; the split-bf16 and 32x32 kernels
-  // address their operands with 32-bit byte offsets
+  // address their operands with 32-bit byte offsets. The 32x32 kernel's loads
+  // run up to 256 k past the end: those offsets must stay past num_records
+  // instead of wrapping back into the operand
   const int64_t lim = ((int64_t)1 << 31) / 4;
-  const int64_t reach = t == kTiny ? std::max<int64_t>(g.K, 32) : 128;
-  const bool near = (g.lda + 1) * reach + g.K < lim && (g.ldb + 1) * reach + g.K < lim;
-  if (!g.B2 && near && (t == kBig || t == kSmall || t == kTiny) && (g.a_kmajor || !g.b_kmajor)) {
+  auto near = [&](int64_t ld, bool kmajor) {
+    const int64_t rows = t == kTiny ? (kmajor ? 32 : g.K + 256) : 128;
+    return (ld + 1) * rows + g.K < lim;
+  };
+  if (!g.B2 && near(g.lda, g.a_kmajor) && near(g.ldb, g.b_kmajor) && (t == kBig || t == kSmall || t == kTiny) &&
+      (g.a_kmajor || !g.b_kmajor)) {
     ORBIT_TRY(gemm_f32_launch(t.BM, g.a_kmajor, g.b_kmajor, a, s));
     return a.splits > 1 ? splitk_finish<float>(g, a, s) : ORBIT_OK;
   }

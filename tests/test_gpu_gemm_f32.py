@@ -105,3 +105,31 @@ def test_gemm_f32_split_bound(lib, x, ak, bk):
     C = _run(lib, torch, A, B, M, N, K, ak, bk)
     ref = K * x * x
     assert float((C.double() - ref).abs().max()) <= 3 * 2.0 ** -24 * ref
+
+
+@pytest.mark.parametrize("ak", [0, 1])
+@pytest.mark.parametrize("ld,tiny", [(1500000, True), (5500000, False)])
+def test_gemm_f32_wide_rows(lib, ak, ld, tiny):
+    """The 32x32 kernel's loads run past K by up to 206 rows, at 32-bit offsets:
+    it is taken only where those cannot wrap back into the operand."""
+    import torch
+    M, N, K = 40, 72, 8
+    buf = torch.empty((K - 1) * ld + 80, device="cuda")
+    a, b = _operands(torch, M, N, K, 1, 0)
+    if ak:
+        A, lda = a, K
+    else:
+        A, lda = torch.empty((K - 1) * ld + M, device="cuda"), ld
+        torch.as_strided(A, (K, M), (ld, 1)).copy_(a.t())
+    torch.as_strided(buf, (K, N), (ld, 1)).copy_(b)
+    C = torch.zeros(M, N, device="cuda")
+    ws = torch.empty(max(16, lib.orbit_gemm_workspace_bytes(0, M, N, K, ak, 0)), dtype=torch.uint8, device="cuda")
+    lib.orbit_timing_filter(None)
+    lib.orbit_timing_enable(True)
+    lib.orbit_gemm(0, M, N, K, A, lda, ak, buf, ld, 0, C, N, 1, 1.0, None, 0, ws)
+    torch.cuda.synchronize()
+    names = lib.orbit_timing_kernel_names()
+    lib.orbit_timing_enable(False)
+    assert ("gemm_f32_tiny" in names) == tiny, names
+    ref = a.double() @ b.double()
+    assert float(((C.double() - ref).abs() / (a.double().abs() @ b.double().abs())).max()) <= K * 2.0 ** -24
