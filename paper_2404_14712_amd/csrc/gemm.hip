@@ -706,14 +706,25 @@ bool on_dma(const Gemm& g) { return g.K >= DBK && g.M > 64 && g.N > 64 && dma_ok
 // a block's waves: latency decides there, and what grows with the product is
 // the tiles' operand traffic, M N K / 4 bytes (512 x 512, K = 512: 10 us against
 // 15 on larger tiles; 512 x 2048, K = 512: 17.6 against 21; but 512 x 512,
-// K = 2048: 30 against 25). The others take 128x128 tiles and the K split with
+// K = 2048: 30 against 25). From eight tiles per CU on a launch is no longer
+// short of blocks and each pays a block's start and end for 1024 outputs (2000 x
+// 1496, K = 64: 14.4 us against 10.4 on 128x128 tiles; 8192 x 8192, K = 8: 176
+// against 60; below eight 0.97 to 2 times as fast over 150 shapes), unless an
+// output is a single tile anyway (4096 products 8 x 4, K = 512: 65 us against
+// 175 on 128x32 tiles). With both operands K-major, K = 1024 and few rows on one
+// side, the rows of the other, 4 KB apart, meet in the same cache sets (16 x
+// 32768: 39 us against 28 on 32x128 tiles; K = 896: 16 x 2632 9.6 against 10.7).
+// The others take 128x128 tiles and the K split with
 // the least modelled time: a round of up to 512 work items (two per CU) costs
 // 5 us + 1.36 us per 16-deep slice, one of up to 256 (one per CU) 5 + 0.80; a
 // split adds a launch and its float32 partials, written and read back (3 us
 // + 0.33 us per MB). Within 5% of the best measured split on 18 block products
 // of 1024 to 8192 rows.
 bool f32_tiny(const Gemm& g) {
-  return g.dtype == ORBIT_F32 && !g.B2 && g.K <= 1024 && (double)g.M * g.N * g.K * g.batch <= 5.5e8;
+  if (g.dtype != ORBIT_F32 || g.B2 || g.K > 1024 || (double)g.M * g.N * g.K * g.batch > 5.5e8) return false;
+  const int64_t each = cdiv(g.M, 32) * cdiv(g.N, 32);
+  if (g.a_kmajor && g.b_kmajor && g.K % 1024 == 0 && each >= 256 && std::min(g.M, g.N) <= 64) return false;
+  return each == 1 || each * g.batch < 2048;
 }
 int f32_splits(const Gemm& g) {
   const int64_t tiles = tiles_of(g, kBig), steps = cdiv(g.K, 16);

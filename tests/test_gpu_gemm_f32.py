@@ -8,10 +8,11 @@ import pytest
 
 pytestmark = pytest.mark.gpu
 
-# M, N, K: below and above the 32x32-tile limit (M N K of 5.5e8, K of 1024); one past tiles
+# M, N, K: below and above the 32x32-tile limits (M N K of 5.5e8, K of 1024, 2048 tiles, few rows
+# of 1024 K-major floats); one past tiles
 # and slices, a single slice, K not a multiple of 16, K split over blocks, 64-wide tiles
 SHAPES = [(8, 8, 8), (40, 72, 24), (264, 136, 512), (520, 1032, 1024), (2056, 136, 2008), (1024, 1024, 1096),
-          (136, 264, 16 * 1024), (4104, 64, 2056)]
+          (136, 264, 16 * 1024), (4104, 64, 2056), (2016, 1024, 64), (2048, 1024, 64), (40, 4104, 1024), (24, 8200, 1024)]
 
 
 def _operands(torch, M, N, K, ak, bk):
