@@ -1539,14 +1539,21 @@ size_t attn_bwd_base_bytes(int B, int H, int L, int dh) {
 }
 
 // float32: the 32-row blocks of attention_f32.hip where the general kernels'
-// 128-row blocks are few. With 128 of those (head_dim 64) the three kernels
-// take 233 against 349 us, with 256 408 against 358: theirs grow with the grid,
-// the general ones' do not below one block per CU. They address a (sample,
-// head) slice with 32-bit byte offsets, up to 160 rows past its end; wider
-// slices stay on the general kernels.
-bool f32_small(const AttnIO& io, int64_t lddo) {
+// 128-row blocks are few. Their time goes up with every round of blocks (one per
+// CU at head_dim 128, two below), the general ones' does not before one block
+// per CU. Measured at 33 to 2048 tokens (general -> small, us): head_dim 128
+// forward 128 blocks of 128 rows 24 -> 24 to 283 -> 166, 160 blocks 25 -> 33 to 284
+// -> 253; backward 64 blocks 47 -> 44 to 971 -> 480, 96 blocks 91 -> 114 to 977 ->
+// 933; head_dim 64 backward 128 blocks 54 -> 50 to 526 -> 316, 160 blocks 55 -> 74
+// to 528 -> 528; its forward at 160 blocks 7.7 -> 8.7 at 33 tokens, 28 -> 26 at 300;
+// head_dim 32 backward 36 -> 38 at 128 tokens, 67 -> 58 at 300. They address a
+// (sample, head) slice with 32-bit byte offsets, up to 160 rows past its end;
+// wider slices stay on the general kernels.
+bool f32_small(const AttnIO& io, int dh, int64_t lddo, bool backward) {
   const int64_t ld = std::max(std::max(io.ldq, io.ldk), std::max(io.ldv, lddo));
-  return cdiv(io.L, 128) * (int64_t)io.H * io.B < 192 && (io.L + 160) * ld * 4 < (int64_t)1 << 31;
+  const int wide = io.L >= 256 ? 191 : 128;
+  const int64_t most = dh == 128 ? (backward ? 64 : 128) : dh == 64 ? (backward ? 128 : wide) : (backward ? wide : 191);
+  return cdiv(io.L, 128) * (int64_t)io.H * io.B <= most && (io.L + 160) * ld * 4 < (int64_t)1 << 31;
 }
 
 template <typename T, int DH>
@@ -1575,7 +1582,7 @@ orbit_status fwd_t(const AttnIO& io, void* o, int64_t ldo, float* lse, float* o3
     return launch(ki, attn_fwd_tr<DH>, dim3((unsigned)cdiv(io.L, 128), io.H, io.B), dim3(256), 0, s, a);
   }
   if constexpr (sizeof(T) == 4) {
-    if (f32_small(io, 0)) {
+    if (f32_small(io, DH, 0, false)) {
       AttnF32Args x{};
       x.q = static_cast<const float*>(io.q); x.k = static_cast<const float*>(io.k); x.v = static_cast<const float*>(io.v);
       x.ldq = io.ldq; x.ldk = io.ldk; x.ldv = io.ldv;
@@ -1625,7 +1632,7 @@ orbit_status bwd_t(const AttnIO& io, const void* o, int64_t ldo, int o_f32, cons
   BwdArgs a{io.q, io.k, io.v, dO, lse, D, qsum, ksum, dq, dk, dv, io.ldq, io.ldk, io.ldv, lddo, ldg, io.H, io.L,
             kLog2e / sqrtf((float)DH), 1.f / sqrtf((float)DH)};
   if constexpr (sizeof(T) == 4) {
-    if (f32_small(io, lddo)) {
+    if (f32_small(io, DH, lddo, true)) {
       AttnF32Args x{};
       x.q = static_cast<const float*>(io.q); x.k = static_cast<const float*>(io.k); x.v = static_cast<const float*>(io.v);
       x.dO = static_cast<const float*>(dO);

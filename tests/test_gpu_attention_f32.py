@@ -1,5 +1,6 @@
 """float32 attention on both sides of the rule that gives small grids 32-row
-blocks (fewer than 192 blocks of 128 rows), against float64.
+blocks (up to 64, 128 or 191 blocks of 128 rows by head_dim, direction and
+length), against float64.
 
 Lengths around the 32-row tiles and the four waves' turns of 128 rows; q, k, v,
 dO and the gradients have different row strides and NaN in the columns past
@@ -14,7 +15,9 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 CASES = [(1, 1, 1, 32), (1, 2, 31, 64), (2, 1, 33, 128), (1, 3, 127, 32), (1, 2, 129, 64), (2, 2, 300, 128),
-         (1, 2, 1030, 64), (3, 63, 128, 32), (3, 64, 128, 32), (2, 96, 129, 64)]
+         (1, 2, 1030, 64), (3, 63, 128, 32), (3, 64, 128, 32), (2, 96, 129, 64),
+         (1, 64, 40, 128), (1, 65, 40, 128), (1, 129, 40, 128), (1, 128, 72, 64), (1, 129, 72, 64), (1, 192, 72, 32),
+         (1, 63, 300, 64), (1, 64, 300, 32)]
 
 
 @pytest.mark.parametrize("B,H,L,dh", CASES)
