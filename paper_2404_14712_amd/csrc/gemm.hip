@@ -653,7 +653,7 @@ bool dma_ok(const Gemm& g) {
          al16(g.A) && al16(g.B);
 }
 
-// bf16 products on gemm_dma_kernel: the (tile, split) pair with the least
+// bf16 products that gemm_dma_kernel takes: the (tile, split) pair with the least
 // modelled time. The model was fitted (least squares on log time) to every tile
 // and split on 144 block products (T = 150 to 8192 tokens, widths 512 to
 // 12288, ragged sizes among them), measured on MI355X. Work items (tile x K
@@ -663,7 +663,14 @@ bool dma_ok(const Gemm& g) {
 // rising from r0 to r5 up to f = 1/2 (fewer CUs busy share the memory system
 // and clock higher), and from rj to r1 above it (with two blocks per CU some
 // CUs then hold two, and they set the time). Input- and weight-gradient
-// layouts scale the step by dx and dw. A split adds a launch and its float32
+// layouts scale the step by dx and dw. With both operands K-major and K no
+// multiple of 32 (rows that start inside a cache line, so that the 64-byte pieces
+// of a slice straddle two) two 128x128 blocks on a CU get in each other's way:
+// their steps cost 1.2 times as much, and gemm_kernel's 128x128 tiles, whose
+// slices are 128 bytes deep, can be the better ones (816 x 8544, K = 7544: 195 us on
+// the DMA kernel's 128x128 tiles, 182 on 256x256, 152 on these; 7056 x 1064, K =
+// 7944: 210, 172 on 256x128, 163; at K below 512 they are not). Over 330 such shapes the choices are within
+// 2% of the best measured pair. A split adds a launch and its float32
 // partials, written and read back. The choices are within 1.1% of the best
 // measured pair in the geometric mean.
 // The 128x128 tile is what short launches needed: with 1770 tokens, 1024 x 1024
@@ -675,12 +682,15 @@ Choice pick_bf16(const Gemm& g) {
   struct Cand { TileCfg t; int slots; double c, r0, r5, rj, r1, dx, dw; };
   const Cand cands[] = {{kDma, 256, 11.57, 0.972, 1.222, 1.127, 1.579, 0.997, 1.060},
                         {kDmaHalf, 512, 9.17, 0.743, 1.087, 1.435, 1.823, 1.023, 1.081},
-                        {kDmaQuarter, 512, 6.89, 0.392, 0.691, 0.953, 1.009, 1.024, 1.030}};
+                        {kDmaQuarter, 512, 6.89, 0.392, 0.691, 0.953, 1.009, 1.024, 1.030},
+                        {kBig, 512, 5.47, 0.850, 1.000, 1.000, 1.197, 1.0, 1.0}};
   Choice best{kDmaQuarter, 1};
   double best_us = 1e300;
+  const bool straddle = g.a_kmajor && g.b_kmajor && g.K % 32 != 0;
   for (const Cand& c : cands) {
-    if (!(c.t == kDmaQuarter) && (g.M < c.t.BM || g.N < c.t.BN)) continue;
+    if (c.t == kBig ? !straddle || g.K < 512 : !(c.t == kDmaQuarter) && (g.M < c.t.BM || g.N < c.t.BN)) continue;
     const double m = g.a_kmajor ? (g.b_kmajor ? c.dx : 1.0) : c.dw;
+    const double two = straddle && c.t == kDmaQuarter ? 1.2 : 1.0;
     const int64_t tiles = tiles_of(g, c.t);
     const int64_t ksteps = cdiv(g.K, 64);
     for (int sp = 1; sp <= 16; sp *= 2) {
@@ -688,8 +698,8 @@ Choice pick_bf16(const Gemm& g) {
       const int64_t items = tiles * sp, full = items / c.slots;
       const double ks = sp > 1 ? (double)cdiv(cdiv(g.K, sp), 64) : (double)g.K / 64.0;
       const double f = (double)(items - full * c.slots) / c.slots;
-      const double r = f <= 0.5 ? c.r0 + (c.r5 - c.r0) * 2.0 * f : c.rj + (c.r1 - c.rj) * (2.0 * f - 1.0);
-      double us = (double)full * (c.c + m * c.r1 * ks) + (f > 0.0 ? c.c + m * r * ks : 0.0);
+      const double r = f <= 0.5 ? c.r0 + (c.r5 - c.r0) * 2.0 * f : two * (c.rj + (c.r1 - c.rj) * (2.0 * f - 1.0));
+      double us = (double)full * (c.c + m * two * c.r1 * ks) + (f > 0.0 ? c.c + m * r * ks : 0.0);
       if (sp > 1) us += 1.82 + sp * (0.117 + 0.234 * (double)g.M * g.N * g.batch * 4.0 / 1e6);
       if (us < best_us) {
         best_us = us;
@@ -773,7 +783,7 @@ int pick_splits(const Gemm& g, const TileCfg& t) {
     const int64_t tiles = tiles_of(g, t), most = cdiv(g.K, 512);
     return (int)std::max<int64_t>(1, std::min<int64_t>(cdiv(128, tiles), std::min<int64_t>(most, 16)));
   }
-  if (t.dma) return pick_bf16(g).splits;
+  if (g.dtype == ORBIT_BF16 && on_dma(g)) return pick_bf16(g).splits;
   if (t == kTiny) return 1;
   if (g.dtype == ORBIT_F32 && t == kBig && !g.B2) return f32_splits(g);
   const int64_t tiles = tiles_of(g, t);

@@ -10,10 +10,11 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 # M, N, K: one past tiles; K of one short slice, of a multiple plus 8, 16 and 24; products whose
-# cost model picks 128, 256x128 and 256x256 tiles with such K
+# cost model picks 128, 256x128 and 256x256 tiles with such K; last, two whose K-major form goes to
+# the register-staged kernel, the second with K split
 SHAPES = [(72, 72, 32), (136, 264, 40), (264, 136, 1000), (152, 768, 2312), (1032, 1048, 1048), (1768, 1024, 1784),
           (4104, 4096, 1064), (520, 6152, 4120),
-          (136, 64, 1032), (1032, 40, 520)]
+          (136, 64, 1032), (1032, 40, 520), (1472, 3560, 1960), (1384, 400, 7032)]
 
 
 @pytest.mark.parametrize("ak,bk", [(1, 0), (1, 1), (0, 0)])
