@@ -591,13 +591,17 @@ orbit_status run_bwd(const bf16* tok, const bf16* dxbar, const bf16* Ut, const f
 
 }  // namespace
 
-// The limits are the kernels' own: 16 heads fill an MFMA tile (8 leave half of
-// it empty), a wave keeps the scores of one 16-variable slot (V <= 128), and
-// the accumulators of 2048 columns fill the registers of a CU. Inside them the
-// pass is faster at every size measured (100 to 8192 patches, 1 to 91
-// variables, 512 to 2048 columns), since it reads half as many bytes.
+// The upper limits are the kernels' own: 16 heads fill an MFMA tile (8 leave half
+// of it empty), a wave keeps the scores of one 16-variable slot (V <= 128), and
+// the accumulators of 2048 columns fill the registers of a CU. Below d = 256 a
+// block works on mostly padded columns: with few variables the forward is
+// slower than the general path's (4096 patches x 2 x 64, 8 heads: 30 -> 37 us; x
+// 12 x 64: 36 -> 38; x 12 x 128: 1.10 times as fast). Inside the limits both
+// directions are faster at every size measured (64 to 8192 patches, 2 to 128
+// variables, 64 to 2048 columns).
 bool agg_stream_ok(orbit_dtype dt, int V, int d, int H) {
-  return dt == ORBIT_BF16 && (H == 8 || H == 16) && V <= kMaxV && d <= kMaxD && d % 8 == 0;
+  return dt == ORBIT_BF16 && (H == 8 || H == 16) && V <= kMaxV && d <= kMaxD && d % 8 == 0 &&
+         (d >= 256 || V * d >= 1024);
 }
 int agg_stream_blocks(int64_t T, int d) { return cpw_of(d) == 64 ? blocks<C64>(T) : blocks<C128>(T); }
 int agg_stream_cols(int d) { return 8 * cpw_of(d); }

@@ -23,7 +23,9 @@ CASES = [
     (1, 20, 31, 1544, 8, 64),      # just past 1536 columns
     (1, 12, 128, 2048, 16, 32),    # the largest V and d
     (1, 270, 2, 2040, 16, 8),
-    (3, 7, 97, 8, 8, 8),           # the smallest d
+    (3, 7, 97, 8, 8, 8),           # the smallest d; few columns: general path
+    (1, 9, 16, 64, 8, 8),          # the fewest columns of the streaming kernels
+    (1, 9, 15, 64, 16, 8),         # just fewer
     (1, 9, 129, 512, 8, 32),       # V past the range: general path
     (1, 9, 20, 2056, 16, 32),      # d past the range: general path
 ]
