@@ -153,15 +153,13 @@ struct SplitStage {
 };
 
 // Both operands M/N-major (weight gradients): waves 0 and 1 stage A, waves 2
-// and 3 B, in blocks of 4 k x BT / 32 rows, so every thread has one block of
-// one operand (4 rows: 16-byte loads; against 2-row blocks of both operands in
+// and 3 B, in blocks of 4 k x 4 rows, so every thread has one block of
+// one operand (16-byte loads; against 2-row blocks of both operands in
 // every thread 4096x1024x8192 went from 468 to 350 us).
-template <int BT>
 struct SplitDual {
-  static constexpr int RW = BT / 32, KC = KD / 4;
-  using V = std::conditional_t<RW == 4, u32x4, u32x2>;
-  static constexpr int PLANE = SplitStage<BT, false>::PLANE;
-  V r[2][4];
+  static constexpr int RW = 4, KC = KD / 4;
+  static constexpr int PLANE = SplitStage<128, false>::PLANE;
+  u32x4 r[2][4];
   unsigned voff;
   int ldb;             // bytes per k
   const float* X;
@@ -183,10 +181,7 @@ struct SplitDual {
     const __amdgpu_buffer_rsrc_t rs =
         buffer_rsrc(reinterpret_cast<const char*>(X) + (int64_t)k0 * ldb, left > 0 ? min(left, KD) * ldb : 0);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if constexpr (RW == 4) r[st][j] = __builtin_amdgcn_raw_buffer_load_b128(rs, voff + (unsigned)(j * ldb), 0, 0);
-      else r[st][j] = __builtin_amdgcn_raw_buffer_load_b64(rs, voff + (unsigned)(j * ldb), 0, 0);
-    }
+    for (int j = 0; j < 4; ++j) r[st][j] = __builtin_amdgcn_raw_buffer_load_b128(rs, voff + (unsigned)(j * ldb), 0, 0);
   }
   ORBIT_DEV void store(int st, bf16* S) const {
 #pragma unroll
@@ -245,9 +240,10 @@ __global__ void __launch_bounds__(256, 2) gemm_f32_kernel(GemmKArgs g) {
   clear();
   {
     constexpr bool DUAL = !AK && !BKM;
+    static_assert(!DUAL || BT == 128, "weight gradients have 128x128 tiles only");
     SA la;
     SB lb;
-    SplitDual<BT> lab;
+    SplitDual lab;
     const float* At = A + (AK ? (int64_t)m0 * g.lda : m0);
     const float* Bt = B + (BKM ? (int64_t)n0 * g.ldb : n0);
     if constexpr (DUAL) {
@@ -517,8 +513,10 @@ orbit_status run(const GemmKArgs& a, hipStream_t s) {
 
 template <int BT>
 orbit_status run_layout(bool ak, bool bk, const GemmKArgs& a, hipStream_t s) {
-  if (ak) return bk ? run<BT, true, true>(a, s) : run<BT, true, false>(a, s);
-  return run<BT, false, false>(a, s);
+  if constexpr (BT == 128) {
+    if (!ak) return run<BT, false, false>(a, s);
+  }
+  return bk ? run<BT, true, true>(a, s) : run<BT, true, false>(a, s);
 }
 
 }  // namespace
