@@ -15,9 +15,13 @@
 // as two groups half a K slice apart, so that one group's MFMAs overlap the
 // other group's fragment reads and copies.
 //
-// Every other product (float32, small or unaligned shapes, concatenated K)
-// runs on gemm_kernel: register-prefetched, double-buffered LDS tiles with
-// K-contiguous staging.
+// float32 products run on gemm_f32.hip's kernels (split into bf16 parts, or
+// 32x32 tiles where they are small). What is left runs on gemm_kernel:
+// register-prefetched, double-buffered LDS tiles with K-contiguous staging.
+// That is, bf16 products of at most 32 rows or columns, with a short or unaligned
+// K or a concatenated one, and some with both operands K-major (pick_bf16);
+// float32 ones of at most 32 rows or columns above the small limit, weight
+// gradients of 33 to 64, a concatenated K, and operands beyond 32-bit offsets.
 #include <stdio.h>
 #include <string>
 
